@@ -7,7 +7,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libllr.so")
-SOURCES = ["llr_sweep.hip", "llr_recon.hip", "llr_mlp.hip", "llr_capi.hip"]
+SOURCES = ["llr_sweep.hip", "llr_chain.hip", "llr_recon.hip", "llr_mlp.hip", "llr_capi.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed FP32 instructions are kept out of the device code
@@ -17,7 +17,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # The sweep kernels are compiled without floating-point contraction: every
 # tile instantiation (links per thread) then performs the same IEEE
 # operations, so results do not depend on the autotuner's choice.
-EXTRA = {"llr_sweep.hip": ["-ffp-contract=off"]}
+EXTRA = {"llr_sweep.hip": ["-ffp-contract=off"], 
+         # the chain-resident kernel loops over the passes of a sweep; left in the
+         # loop, the polynomials' constants cost an instruction each, hoisted out
+         # of it they fill the registers and spill
+         "llr_chain.hip": ["-ffp-contract=off", "-mllvm", "-disable-machine-licm"]}
 
 
 def _compile(src):

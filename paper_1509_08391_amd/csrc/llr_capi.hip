@@ -95,6 +95,7 @@ struct llr_ctx {
     LatTable lt{};
     DevState ds{};
     bool laid_out = false;
+    bool resident = false;     // every lattice's chain fits in LDS (chain-resident sweeps)
     void* state = nullptr;
     size_t state_bytes = 0;
     bool have_energy = false;
@@ -301,7 +302,7 @@ static llr_status layout(llr_ctx* c) {
     AL(cen, n) AL(w, n) AL(sumE, n) AL(conf, n) AL(conv_iter, n) AL(conv_sweeps, n) AL(mu_lnrho, n)
     AL(mu_b, kMaxLat) AL(link_fix, n) AL(link_arc, n)
     AL(lat_done, kMaxLat) AL(lat_outside, kMaxLat) AL(lat_approach, kMaxLat) AL(sweep_ctr, 1)
-    AL(approach_ctr, 1) AL(rm_iter, 1) AL(re_cnt, 2) AL(bits_row, 1)
+    AL(approach_ctr, 1) AL(arrive, 1) AL(rm_iter, 1) AL(re_cnt, 2) AL(bits_row, 1)
 #undef AL
     s.a_hist = nullptr;
     s.bits_log = nullptr;
@@ -313,6 +314,8 @@ static llr_status layout(llr_ctx* c) {
     for (int i = 0; i < n; ++i) ident[i] = i;
     HIPCHK(hipMemcpyAsync(s.itv, ident.data(), n * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(s.conf, ident.data(), n * 4, hipMemcpyHostToDevice, c->stream));
+    c->resident = chain_fits(lt, elem_size(c));
+    if (c->resident) HIPCHK(chain_setup());
     c->approach_sweeps.assign(lt.n, 0);
     c->laid_out = true;
     return upload_intervals(c);
@@ -406,17 +409,65 @@ static void enqueue_energy(llr_ctx* c, int check = kCheckDrift) {
 
 // the overrelaxation class passes one sweep applies to every chain: 8
 // plain ones, or 8 fused into the heatbath passes
-static void note_sweep(llr_ctx* c, bool fused) {
+static void note_sweep(llr_ctx* c, bool fused, int n = 1) {
     if (c->capturing) return;
-    c->sweeps_run += 1;
-    if (fused) c->fused_passes += 8;
-    else c->or_passes += 8;
+    c->sweeps_run += n;
+    if (fused) c->fused_passes += 8 * (long long)n;
+    else c->or_passes += 8 * (long long)n;
 }
 
-// one restricted sweep of all chains, then recompute / replica exchange / measurement
+static bool plain_mode(int mode) {
+    return mode == LLR_MODE_RESTRICTED || mode == LLR_MODE_FREE || mode == LLR_MODE_MUCA;
+}
+
+// Whether sweeps of this mode run chain-resident: every chain fits in LDS, the
+// links of a class are drawn independently, and no per-kernel timing is asked
+// for (its figures are those of the class-pass kernels).
+static bool resident_sweeps(const llr_ctx* c, int mode) {
+    return c->resident && !c->timing && (plain_mode(mode) || mode == LLR_MODE_APPROACH);
+}
+
+static int recompute_check(int mode) {
+    return kCheckDrift | (mode == LLR_MODE_RESTRICTED || mode == LLR_MODE_LINK ? kCheckInterval : 0);
+}
+
+static ChainArgs chain_args(const llr_ctx* c, int mode, int n) {
+    ChainArgs a{};
+    a.mode = mode;
+    a.order = c->interleave ? 1 : (c->stagger ? 2 : 0);
+    if (!plain_mode(mode)) a.order = 0;
+    a.n_sweeps = n;
+    a.last = -1;
+    a.check = recompute_check(mode);
+    a.measure_from = n;
+    a.end_sweep = 1;
+    a.k0 = (uint32_t)c->prm.seed;
+    a.k1 = (uint32_t)(c->prm.seed >> 32);
+    return a;
+}
 template <typename T>
-static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bool measure) {
-    const bool plain = mode == LLR_MODE_RESTRICTED || mode == LLR_MODE_FREE || mode == LLR_MODE_MUCA;
+static void enqueue_chain(llr_ctx* c, const ChainArgs& a) {
+    if (!a.approach) note_sweep(c, a.order == 1, a.n_sweeps);
+    launch_chain<T>(c->lt, (T*)c->state, c->ds, a, c->stream);
+}
+// sweeps of one chain-resident launch: bounds a launch's duration
+constexpr int kChainSweeps = 64;
+
+// one restricted sweep of all chains, then recompute / replica exchange /
+// measurement; E_row, b_row: device rows for the sweep's E and accept bits
+template <typename T>
+static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bool measure, double* E_row = nullptr,
+                          uint16_t* b_row = nullptr) {
+    if (resident_sweeps(c, mode) && mode != LLR_MODE_APPROACH) {
+        ChainArgs a = chain_args(c, mode, 1);
+        a.every = recompute ? 1 : 0;
+        a.end_sweep = 0;
+        enqueue_chain<T>(c, a);
+        if (replica) launch_replica(c->lt, c->ds, a.k0, a.k1, c->stream);
+        launch_end_sweep(c->lt, c->ds, measure ? 1 : 0, 0, 1, E_row, b_row, c->stream);
+        return;
+    }
+    const bool plain = plain_mode(mode);
     const bool fused = c->interleave && plain;
     note_sweep(c, fused);
     if (fused) {
@@ -455,10 +506,9 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
             for (int col = 0; col < 8; ++col) enqueue_or_pass<T>(c, col);
         }
     }
-    if (recompute)
-        enqueue_energy<T>(c, kCheckDrift | (mode == LLR_MODE_RESTRICTED || mode == LLR_MODE_LINK ? kCheckInterval : 0));
+    if (recompute) enqueue_energy<T>(c, recompute_check(mode));
     if (replica) launch_replica(c->lt, c->ds, (uint32_t)c->prm.seed, (uint32_t)(c->prm.seed >> 32), c->stream);
-    launch_end_sweep(c->lt, c->ds, measure ? 1 : 0, 0, 1, c->stream);
+    launch_end_sweep(c->lt, c->ds, measure ? 1 : 0, 0, 1, E_row, b_row, c->stream);
 }
 
 static llr_status ensure_link_buffers(llr_ctx* c);
@@ -512,7 +562,20 @@ static llr_status launch_sweep(llr_ctx* c, bool recompute, bool replica, bool me
 template <typename T>
 static void enqueue_approach_sweep(llr_ctx* c) {
     for (int col = 0; col < 8; ++col) enqueue_hb_pass<T>(c, col, LLR_MODE_APPROACH, kApproach);
-    launch_end_sweep(c->lt, c->ds, 0, 1, 0, c->stream);
+    launch_end_sweep(c->lt, c->ds, 0, 1, 0, nullptr, nullptr, c->stream);
+}
+
+template <typename T>
+static void enqueue_approach_block(llr_ctx* c, int n) {
+    if (!resident_sweeps(c, LLR_MODE_APPROACH)) {
+        for (int j = 0; j < n; ++j) enqueue_approach_sweep<T>(c);
+        return;
+    }
+    for (int j = 0; j < n; j += kChainSweeps) {
+        ChainArgs a = chain_args(c, LLR_MODE_APPROACH, std::min(kChainSweeps, n - j));
+        a.approach = 1;
+        enqueue_chain<T>(c, a);
+    }
 }
 
 // Autotuner: class links per thread (1, 2, 4) of the heatbath and the
@@ -611,7 +674,7 @@ static llr_status approach_continue_impl(llr_ctx* c, long long max_sweeps, int* 
     for (int i = 0; i < c->lt.n; ++i) all = all && c->ap_done[i];
     long long t = 0;
     while (!all && t < max_sweeps) {
-        for (int j = 0; j < K; ++j) enqueue_approach_sweep<T>(c);
+        enqueue_approach_block<T>(c, K);
         enqueue_energy<T>(c);
         for (int i = 0; i < c->lt.n; ++i)
             if (!c->ap_done[i]) c->approach_sweeps[i] += K;
@@ -682,8 +745,19 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
     const int nsw = p.n_th + p.n_a;
     RunCfg cfg{(uint32_t)p.seed, (uint32_t)(p.seed >> 32), p.n_a, nsw, p.eps};
     llr_status st = LLR_OK;
+    // without replica exchange nothing couples the chains between sweeps
+    const bool chunks = resident_sweeps(c, restricted_mode(c)) && !p.replica_exchange;
     for (int it = 0; it < iters; ++it) {
-        for (int j = 0; j < nsw; ++j) {
+        for (int j = 0; chunks && j < nsw; j += kChainSweeps) {
+            ChainArgs a = chain_args(c, restricted_mode(c), std::min(kChainSweeps, nsw - j));
+            a.j0 = j;
+            a.every = K;
+            a.last = nsw - 1;
+            a.measure_from = std::max(0, p.n_th - j);
+            enqueue_chain<T>(c, a);
+            if ((j / kChainSweeps & 15) == 15) HIPCHK(hipStreamSynchronize(c->stream));   // bound the queue depth
+        }
+        for (int j = 0; !chunks && j < nsw; ++j) {
             const bool rec = ((j + 1) % K == 0) || (j == nsw - 1);
             st = launch_sweep<T>(c, rec, p.replica_exchange != 0, j >= p.n_th);
             if (st != LLR_OK) return st;
@@ -716,33 +790,54 @@ static llr_status run_impl(llr_ctx* c) {
     return rm_converged(c);
 }
 
-template <typename T>
-static llr_status sweeps_impl(llr_ctx* c, int n_sweeps, long long sweep0, int mode, uint16_t* bits) {
-    const uint32_t s0 = (uint32_t)sweep0;
-    HIPCHK(hipMemcpyAsync(c->ds.sweep_ctr, &s0, 4, hipMemcpyHostToDevice, c->stream));
-    const int n = c->lt.n_chains;
-    for (int t = 0; t < n_sweeps; ++t) {
-        enqueue_sweep<T>(c, mode, false, false, false);
-        if (bits) {
-            HIPCHK(hipMemcpyAsync(bits + (size_t)t * n, c->ds.bits_last, 2 * n, hipMemcpyDeviceToHost, c->stream));
-        }
-    }
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    if (c->timing) harvest(c);
-    return health_check(c);
+// Rows of per-sweep results kept on the device before they are copied to the
+// host in one piece (a copy to pageable host memory waits for the stream, so
+// one per sweep would leave the GPU idle between sweeps).
+static int history_rows(int n_chains, int n_sweeps, size_t bytes_per_chain) {
+    const size_t row = bytes_per_chain * (size_t)n_chains;
+    return (int)std::min<size_t>((size_t)n_sweeps, std::max<size_t>(1, ((size_t)4 << 20) / row));
 }
 
+// n_sweeps sweeps from sweep index sweep0 in the given mode, recompute after
+// every K-th (0: never); E_hist, bits (host, optional): per sweep and chain
 template <typename T>
-static llr_status muca_sweeps_impl(llr_ctx* c, int n_sweeps, long long sweep0, double* E_hist) {
+static llr_status plain_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, int mode, int K, double* E_hist,
+                               uint16_t* bits) {
     const uint32_t s0 = (uint32_t)sweep0;
     HIPCHK(hipMemcpyAsync(c->ds.sweep_ctr, &s0, 4, hipMemcpyHostToDevice, c->stream));
     const int n = c->lt.n_chains;
-    const int K = c->prm.recompute_every;
-    for (int t = 0; t < n_sweeps; ++t) {
-        enqueue_sweep<T>(c, LLR_MODE_MUCA, K > 0 && (t + 1) % K == 0, false, false);
-        if (E_hist) HIPCHK(hipMemcpyAsync(E_hist + (size_t)t * n, c->ds.E, 8 * (size_t)n, hipMemcpyDeviceToHost,
+    const size_t entry = (E_hist ? 8 : 0) + (bits ? 2 : 0);
+    const int rows = entry ? history_rows(n, n_sweeps, entry) : n_sweeps;
+    double* dE = nullptr;
+    uint16_t* dB = nullptr;
+    if (entry && n_sweeps > 0) {
+        llr_status st = ensure_stage(c, entry * (size_t)rows * n + 64);
+        if (st != LLR_OK) return st;
+        if (E_hist) dE = (double*)c->stage;
+        if (bits) dB = (uint16_t*)((char*)c->stage + (E_hist ? 8 * (size_t)rows * n : 0));
+    }
+    const bool chunks = resident_sweeps(c, mode) && mode != LLR_MODE_APPROACH;
+    for (int t0 = 0; t0 < n_sweeps; t0 += rows) {
+        const int m = std::min(rows, n_sweeps - t0);
+        for (int t = 0; t < m;) {
+            double* eRow = dE ? dE + (size_t)t * n : nullptr;
+            uint16_t* bRow = dB ? dB + (size_t)t * n : nullptr;
+            if (chunks) {
+                ChainArgs a = chain_args(c, mode, std::min(kChainSweeps, m - t));
+                a.j0 = t0 + t;
+                a.every = K;
+                a.E_hist = eRow;
+                a.bits_hist = bRow;
+                enqueue_chain<T>(c, a);
+                t += a.n_sweeps;
+            } else {
+                enqueue_sweep<T>(c, mode, K > 0 && (t0 + t + 1) % K == 0, false, false, eRow, bRow);
+                ++t;
+            }
+        }
+        if (E_hist) HIPCHK(hipMemcpyAsync(E_hist + (size_t)t0 * n, dE, 8 * (size_t)m * n, hipMemcpyDeviceToHost,
                                           c->stream));
+        if (bits) HIPCHK(hipMemcpyAsync(bits + (size_t)t0 * n, dB, 2 * (size_t)m * n, hipMemcpyDeviceToHost, c->stream));
     }
     HIPCHK(hipStreamSynchronize(c->stream));
     HIPCHK(hipGetLastError());
@@ -759,23 +854,29 @@ static llr_status observables_impl(llr_ctx* c, int n_meas, int gap, long long sw
     const uint32_t s0 = (uint32_t)sweep0;
     HIPCHK(hipMemcpyAsync(c->ds.sweep_ctr, &s0, 4, hipMemcpyHostToDevice, c->stream));
     const int n = c->lt.n_chains;
-    std::vector<double> E(n), B(n);
-    std::vector<int> conf(n);
-    for (int m = 0; m < n_meas; ++m) {
-        for (int t = 0; t < gap; ++t)
-            enqueue_sweep<T>(c, restricted_mode(c), false, c->prm.replica_exchange != 0, false);
-        {
-            TimeScope ts(c, 2);
-            launch_energy<T>(c->lt, (const T*)c->state, c->ds, c->stream, true, kCheckDrift | kCheckInterval);
+    const int rows = history_rows(n, n_meas, 16);
+    llr_status st = ensure_stage(c, 16 * (size_t)rows * n + 64);
+    if (st != LLR_OK) return st;
+    double* dE = (double*)c->stage;
+    double* dB = dE + (size_t)rows * n;
+    const int mode = restricted_mode(c);
+    const bool chunks = resident_sweeps(c, mode) && !c->prm.replica_exchange;
+    for (int m0 = 0; m0 < n_meas; m0 += rows) {
+        const int nm = std::min(rows, n_meas - m0);
+        for (int m = 0; m < nm; ++m) {
+            for (int t = 0; chunks && t < gap; t += kChainSweeps)
+                enqueue_chain<T>(c, chain_args(c, mode, std::min(kChainSweeps, gap - t)));
+            for (int t = 0; !chunks && t < gap; ++t)
+                enqueue_sweep<T>(c, mode, false, c->prm.replica_exchange != 0, false);
+            {
+                TimeScope ts(c, 2);
+                launch_energy<T>(c->lt, (const T*)c->state, c->ds, c->stream, true, kCheckDrift | kCheckInterval);
+            }
+            launch_obs_row(c->lt, c->ds, dE + (size_t)m * n, dB + (size_t)m * n, c->stream);
         }
-        HIPCHK(hipMemcpyAsync(E.data(), c->ds.E, 8 * (size_t)n, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipMemcpyAsync(B.data(), c->ds.obs, 8 * (size_t)n, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipMemcpyAsync(conf.data(), c->ds.conf, 4 * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipMemcpyAsync(E_out + (size_t)m0 * n, dE, 8 * (size_t)nm * n, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipMemcpyAsync(B_out + (size_t)m0 * n, dB, 8 * (size_t)nm * n, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
-        for (int k = 0; k < n; ++k) {
-            E_out[(size_t)m * n + k] = E[conf[k]];
-            B_out[(size_t)m * n + k] = B[conf[k]];
-        }
     }
     HIPCHK(hipGetLastError());
     if (c->timing) harvest(c);
@@ -1129,8 +1230,8 @@ llr_status llr_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, int mode, uint
         return fail(LLR_EINVAL, "bad n_sweeps or mode");
     HIPCHK(hipSetDevice(c->device));
     if (mode == LLR_MODE_LINK && (st = ensure_link_buffers(c)) != LLR_OK) return st;
-    return c->precision == LLR_FP32 ? sweeps_impl<float>(c, n_sweeps, sweep0, mode, bits)
-                                    : sweeps_impl<double>(c, n_sweeps, sweep0, mode, bits);
+    return c->precision == LLR_FP32 ? plain_sweeps<float>(c, n_sweeps, sweep0, mode, 0, nullptr, bits)
+                                    : plain_sweeps<double>(c, n_sweeps, sweep0, mode, 0, nullptr, bits);
 }
 
 llr_status llr_class_pass(llr_ctx* c, int heatbath, int colour, int mode, long long sweep_index) {
@@ -1570,8 +1671,8 @@ llr_status llr_muca_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, double* E
     if (!c->muca_ready) return fail(LLR_ESTATE, "call llr_muca_begin first");
     if (n_sweeps < 0) return fail(LLR_EINVAL, "bad n_sweeps");
     HIPCHK(hipSetDevice(c->device));
-    return c->precision == LLR_FP32 ? muca_sweeps_impl<float>(c, n_sweeps, sweep0, E_hist)
-                                    : muca_sweeps_impl<double>(c, n_sweeps, sweep0, E_hist);
+    return c->precision == LLR_FP32 ? plain_sweeps<float>(c, n_sweeps, sweep0, LLR_MODE_MUCA, c->prm.recompute_every, E_hist, nullptr)
+                                    : plain_sweeps<double>(c, n_sweeps, sweep0, LLR_MODE_MUCA, c->prm.recompute_every, E_hist, nullptr);
 }
 
 llr_status llr_muca_reweight(llr_ctx* c, const double* E, long m, const double* centres, const double* a, int n,

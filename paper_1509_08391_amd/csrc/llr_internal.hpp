@@ -93,6 +93,7 @@ struct DevState {
     uint32_t* approach_ctr;
     int* rm_iter;          // current RM iteration n
     unsigned long long* re_cnt;  // [proposed, accepted]
+    uint32_t* arrive;      // blocks of a chain-resident launch that have finished (0 between launches)
     uint16_t* bits_log;    // optional, rows x n_chains
     long long* bits_row;   // next log row
     long long bits_rows_max;
@@ -113,6 +114,26 @@ struct RunCfg {
     double eps;
 };
 
+// One launch of the chain-resident sweep (llr_chain.hip).
+struct ChainArgs {
+    int mode, approach;    // kMode*; approach sweeps use their own counters and no overrelaxation
+    int order;             // 0 grouped, 1 interleaved, 2 staggered
+    int n_sweeps;
+    int j0, every, last;   // recompute E after sweep j0 + t where every divides its index + 1, and after `last`
+    int check;             // kCheck* of the recompute
+    int measure_from;      // first sweep of the launch whose E is accumulated
+    int end_sweep;         // log the accept bits and advance the counters (0: k_end_sweep follows)
+    uint32_t k0, k1;       // Philox key
+    double* E_hist;        // optional, n_sweeps x chains: E after every sweep
+    uint16_t* bits_hist;   // optional, n_sweeps x chains: accept bits of every sweep
+};
+
+// chain-resident sweeps (llr_chain.hip): whether every lattice's chain fits in
+// LDS, and the launch (one block per chain)
+bool chain_fits(const LatTable& lt, size_t elem);
+hipError_t chain_setup();
+template <typename T> void launch_chain(const LatTable& lt, T* th, DevState s, const ChainArgs& a, hipStream_t st);
+
 // launchers (llr_sweep.hip); T = float or double
 template <typename T> void launch_hot_start(const LatTable& lt, T* th, DevState s, uint32_t k0, uint32_t k1, hipStream_t st);
 template <typename T> void launch_hb_pass(const LatTable& lt, T* th, DevState s, int colour, int mode, int kind,
@@ -128,7 +149,11 @@ template <typename T> void launch_energy(const LatTable& lt, const T* th, DevSta
                                           bool with_obs = false, int check = 0);
 template <typename T> void launch_export(const LatTable& lt, int li, const T* th, DevState s, T* out, hipStream_t st);
 template <typename T> void launch_import(const LatTable& lt, int li, T* th, DevState s, const T* in, hipStream_t st);
-void launch_end_sweep(const LatTable& lt, DevState s, int measure, int approach, int with_or, hipStream_t st);
+// E_row, b_row (optional, one entry per chain): the sweep's E and accept bits
+void launch_end_sweep(const LatTable& lt, DevState s, int measure, int approach, int with_or, double* E_row,
+                      uint16_t* b_row, hipStream_t st);
+// E and the adjoint plaquette sum of the chain serving each interval
+void launch_obs_row(const LatTable& lt, DevState s, double* E_row, double* B_row, hipStream_t st);
 void launch_replica(const LatTable& lt, DevState s, uint32_t k0, uint32_t k1, hipStream_t st);
 void launch_rm_update(const LatTable& lt, DevState s, RunCfg cfg, hipStream_t st);
 void launch_approach_init(const LatTable& lt, DevState s, hipStream_t st);
