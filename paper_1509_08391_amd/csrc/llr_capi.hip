@@ -1940,20 +1940,48 @@ llr_status llr_mlp_warm_start(llr_ctx* c, int lat, const float* w, int bf16, dou
     return LLR_OK;
 }
 
+// Device workspace of the training behind the inputs of stage_inputs: two sets
+// of parameters and moments, two of the chunks' partial gradients, the chunks'
+// parts of every epoch's loss and the losses.
+struct MlpWork {
+    MlpBuf buf[2];
+    float* part[2];
+    double *loss_part, *loss;
+    static size_t bytes(int n, int epochs) {
+        const size_t nc = (size_t)mlp_chunks(n);
+        return 4 * (size_t)kMlpNP * (6 + 2 * nc) + 8 * (size_t)epochs * (nc + 1) + 64;
+    }
+    MlpWork(void* base, int n, int epochs) {
+        const size_t nc = (size_t)mlp_chunks(n);
+        loss_part = (double*)(((uintptr_t)base + 7) & ~(uintptr_t)7);
+        loss = loss_part + (size_t)epochs * nc;
+        float* p = (float*)(loss + epochs);
+        for (auto& b : buf) {
+            b = {p, p + kMlpNP, p + 2 * kMlpNP};
+            p += 3 * kMlpNP;
+        }
+        for (auto& q : part) {
+            q = p;
+            p += nc * kMlpNP;
+        }
+    }
+};
+
 llr_status llr_mlp_loss_grad(llr_ctx* c, const float* w, const float* u, const float* invL, const double* a, int n,
                              int bf16, float* grad, double* loss) {
     if (!c || !w || !u || !invL || !a || !grad || !loss || n < 1 || n > 4096) return fail(LLR_EINVAL, "bad argument");
     HIPCHK(hipSetDevice(c->device));
     float *dw, *du, *dl;
     double* dA;
-    llr_status st = stage_inputs(c, w, u, invL, a, n, &dw, &du, &dl, &dA, 4 * (size_t)kMlpNP + 64);
+    llr_status st = stage_inputs(c, w, u, invL, a, n, &dw, &du, &dl, &dA, MlpWork::bytes(n, 1));
     if (st != LLR_OK) return st;
-    float* dg = (float*)(dA + n);
-    double* dloss = (double*)(dg + kMlpNP + 2);
-    dloss = (double*)(((uintptr_t)dloss + 7) & ~(uintptr_t)7);
-    launch_mlp_loss_grad(dw, du, dl, dA, n, bf16, dg, dloss, c->stream);
-    HIPCHK(hipMemcpyAsync(grad, dg, 4 * kMlpNP, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(loss, dloss, 8, hipMemcpyDeviceToHost, c->stream));
+    const MlpWork k(dA + n, n, 1);
+    launch_mlp_epoch({dw, nullptr, nullptr}, k.buf[0], nullptr, 0, 0.f, du, dl, dA, n, bf16, k.part[0], k.loss_part,
+                     c->stream);
+    launch_mlp_adam(k.buf[0], k.buf[0], k.part[0], n, 0, 0.f, c->stream);
+    launch_mlp_loss(k.loss_part, n, 1, k.loss, c->stream);
+    HIPCHK(hipMemcpyAsync(grad, k.buf[0].w, 4 * kMlpNP, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipMemcpyAsync(loss, k.loss, 8, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     HIPCHK(hipGetLastError());
     return LLR_OK;
@@ -1966,20 +1994,29 @@ llr_status llr_mlp_train(llr_ctx* c, float* w, const float* u, const float* invL
     HIPCHK(hipSetDevice(c->device));
     float *dw, *du, *dl;
     double* dA;
-    const size_t extra = 4 * 3 * (size_t)kMlpNP + 8 * (size_t)std::max(epochs, 1) + 256;
-    llr_status st = stage_inputs(c, w, u, invL, a, n, &dw, &du, &dl, &dA, extra);
+    const int ne = std::max(epochs, 1);
+    llr_status st = stage_inputs(c, w, u, invL, a, n, &dw, &du, &dl, &dA, MlpWork::bytes(n, ne));
     if (st != LLR_OK) return st;
-    float* dg = (float*)(dA + n);
-    float* dm = dg + kMlpNP;
-    float* dv = dm + kMlpNP;
-    double* dloss = (double*)(((uintptr_t)(dv + kMlpNP) + 7) & ~(uintptr_t)7);
-    HIPCHK(hipMemsetAsync(dm, 0, 4 * 2 * (size_t)kMlpNP, c->stream));
+    const MlpWork k(dA + n, n, ne);
+    const int nc = mlp_chunks(n);
+    HIPCHK(hipMemcpyAsync(k.buf[0].w, dw, 4 * kMlpNP, hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(hipMemsetAsync(k.buf[0].m, 0, 4 * 2 * (size_t)kMlpNP, c->stream));
+    // Adam inside the next epoch's launch while every block can afford to sum
+    // all chunks' gradients itself (us per epoch fused / separate: 40 samples
+    // 15.2 / 16.4, 160 16.7 / 17.1, 512 17.7 / 18.5); beyond that the blocks'
+    // reads grow with the square of the chunks, and Adam gets a launch of its own
+    const bool in_epoch = nc <= kMlpFuseChunks;
+    int cur = 0;
     for (int e = 0; e < epochs; ++e) {
-        launch_mlp_loss_grad(dw, du, dl, dA, n, bf16, dg, dloss + e, c->stream);
-        launch_mlp_adam(dw, dm, dv, dg, e + 1, lr, c->stream);
+        const int t = in_epoch ? e : 0;
+        launch_mlp_epoch(k.buf[cur], k.buf[cur ^ 1], k.part[(e + 1) & 1], t, lr, du, dl, dA, n, bf16, k.part[e & 1],
+                         k.loss_part + (size_t)e * nc, c->stream);
+        if (t > 0) cur ^= 1;
+        if (!in_epoch || e == epochs - 1) launch_mlp_adam(k.buf[cur], k.buf[cur], k.part[e & 1], n, e + 1, lr, c->stream);
     }
-    HIPCHK(hipMemcpyAsync(w, dw, 4 * kMlpNP, hipMemcpyDeviceToHost, c->stream));
-    if (loss_hist && epochs > 0) HIPCHK(hipMemcpyAsync(loss_hist, dloss, 8 * (size_t)epochs, hipMemcpyDeviceToHost, c->stream));
+    if (epochs > 0) launch_mlp_loss(k.loss_part, n, epochs, k.loss, c->stream);
+    HIPCHK(hipMemcpyAsync(w, k.buf[cur].w, 4 * kMlpNP, hipMemcpyDeviceToHost, c->stream));
+    if (loss_hist && epochs > 0) HIPCHK(hipMemcpyAsync(loss_hist, k.loss, 8 * (size_t)epochs, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     HIPCHK(hipGetLastError());
     return LLR_OK;

@@ -185,8 +185,15 @@ constexpr int kMlpNP = 4417;
 void launch_mlp_init(uint64_t seed, float* w, hipStream_t st);
 void launch_mlp_forward(const float* w, const float* u, const float* invL, int n, int bf16, double* a_out,
                         hipStream_t st);
-void launch_mlp_loss_grad(const float* w, const float* u, const float* invL, const double* a, int n, int bf16,
-                          float* grad, double* loss, hipStream_t st);
-void launch_mlp_adam(float* w, float* m, float* v, const float* g, int t, float lr, hipStream_t st);
+// training: kMlpRows samples per chunk, each chunk's gradient in a row of its own
+constexpr int kMlpRows = 64;
+inline int mlp_chunks(int n) { return (n + kMlpRows - 1) / kMlpRows; }
+constexpr int kMlpFuseChunks = 8;       // at most this many chunks: Adam inside the next epoch's launch
+struct MlpBuf { float *w, *m, *v; };   // parameters and Adam's moments
+void launch_mlp_epoch(MlpBuf in, MlpBuf out, const float* part_in, int t_adam, float lr, const float* u,
+                      const float* invL, const double* a, int n, int bf16, float* part_out, double* loss_part,
+                      hipStream_t st);
+void launch_mlp_adam(MlpBuf in, MlpBuf out, const float* part, int n, int t, float lr, hipStream_t st);
+void launch_mlp_loss(const double* loss_part, int n, int epochs, double* loss, hipStream_t st);
 
 }  // namespace llr
