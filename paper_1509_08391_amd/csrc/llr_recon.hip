@@ -12,18 +12,253 @@ namespace llr {
 
 constexpr int kRB = 256;
 
-// The recursion is sequential by definition: one thread per set of a_k
-// (row r of a and of L at offset r n).
-__global__ void k_lnrho(const double* __restrict__ a, int n, int rows, double s, double* __restrict__ L) {
-    const int r = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (r >= rows) return;
-    const double* ar = a + (size_t)r * n;
-    double* Lr = L + (size_t)r * n;
+// ln rho at n centres into L (LDS or global): the recursion is sequential by
+// definition, so one thread adds, but the whole block loads the terms, kTerms
+// at a time, into LDS first (a thread that also loads waits for memory at every
+// step: 20 us at n = 128, against 2).  Every caller's block has kRB threads.
+constexpr int kTerms = 1024;
+
+template <typename F>
+__device__ __forceinline__ void scan_lnrho(const double* __restrict__ a, int n, double s, double* term, F&& store) {
     double v = 0.0;
-    Lr[0] = 0.0;
-    for (int k = 0; k + 1 < n; ++k) {
-        v = v - 0.5 * s * (ar[k] + ar[k + 1]);
-        Lr[k + 1] = v;
+    const double f = -(0.5 * s);
+    for (int k0 = 0; k0 < n; k0 += kTerms) {
+        const int m = min(kTerms, n - k0);
+        for (int i = threadIdx.x; i < m; i += kRB) {
+            const int k = k0 + i;
+            term[i] = k == 0 ? 0.0 : a[k - 1] + a[k];
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int i = 0;
+            for (; i + 8 <= m; i += 8) {
+                double t[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) t[q] = term[i + q];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    v = __fma_rn(f, t[q], v);
+                    term[i + q] = v;
+                }
+            }
+            for (; i < m; ++i) {
+                v = __fma_rn(f, term[i], v);
+                term[i] = v;
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < m; i += kRB) store(k0 + i, term[i]);
+        __syncthreads();
+    }
+}
+
+// one block per set of a_k (row r of a and of L at offset r n)
+__global__ __launch_bounds__(kRB) void k_lnrho(const double* __restrict__ a, int n, double s, double* __restrict__ L) {
+    __shared__ double term[kTerms];
+    const size_t r = (size_t)blockIdx.x * (size_t)n;
+    scan_lnrho(a + r, n, s, term, [&](int k, double v) { L[r + k] = v; });
+}
+
+// ---------------------------------------------------------------------------
+// Moments of up to kRowN intervals in registers.  A block-wide reduction per
+// sum (four per point, two barriers each) and a second exponential per interval
+// made a grid point cost more in barriers than in arithmetic; here G = 16 lanes
+// (one DPP row, reduced by rotations) or a whole wavefront hold one point's
+// terms, KP per lane, and compute each exponential once.
+// ---------------------------------------------------------------------------
+constexpr int kRowN = 512;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// over the 16 lanes of a row, the same value on all of them (row_ror:8, 4, 2, 1)
+__device__ __forceinline__ double row_sum(double v) {
+    v += dpp_f64<0x128>(v);
+    v += dpp_f64<0x124>(v);
+    v += dpp_f64<0x122>(v);
+    return v + dpp_f64<0x121>(v);
+}
+__device__ __forceinline__ double row_max(double v) {
+    v = fmax(v, dpp_f64<0x128>(v));
+    v = fmax(v, dpp_f64<0x124>(v));
+    v = fmax(v, dpp_f64<0x122>(v));
+    return fmax(v, dpp_f64<0x121>(v));
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+template <int G>
+__device__ __forceinline__ double grp_sum(double v) {
+    v = row_sum(v);
+    if constexpr (G == 64) v = (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+    return v;
+}
+template <int G>
+__device__ __forceinline__ double grp_max(double v) {
+    v = row_max(v);
+    if constexpr (G == 64) v = fmax(fmax(lane_f64(v, 0), lane_f64(v, 16)), fmax(lane_f64(v, 32), lane_f64(v, 48)));
+    return v;
+}
+
+// (mean, variance) of E at coupling beta; c, L: this lane's terms (an absent
+// one has c = 0, L = -inf)
+template <int KP, int G>
+__device__ __forceinline__ void lane_moments(const double (&c)[KP], const double (&L)[KP], double beta, double* mean,
+                                             double* var) {
+    double w[KP], m = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+        w[q] = __fma_rn(beta, c[q], L[q]);
+        m = fmax(m, w[q]);
+    }
+    m = grp_max<G>(m);
+    double z = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+        w[q] = exp(w[q] - m);
+        z += w[q];
+        s1 = __fma_rn(w[q], c[q], s1);
+    }
+    z = grp_sum<G>(z);
+    s1 = grp_sum<G>(s1);
+    const double mu = s1 / z;
+    double s2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+        const double d = c[q] - mu;
+        s2 = __fma_rn(w[q] * d, d, s2);
+    }
+    *mean = mu;
+    *var = grp_sum<G>(s2) / z;
+}
+
+// this lane's terms of a row whose ln rho is in LDS: intervals lane, lane + G, ...
+template <int KP, int G>
+__device__ __forceinline__ void lane_terms(const double* __restrict__ c, const double* Ls, int n, int lane,
+                                           double (&cr)[KP], double (&Lr)[KP]) {
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+        const int k = lane + q * G;
+        cr[q] = k < n ? c[k] : 0.0;
+        Lr[q] = k < n ? Ls[k] : -INFINITY;
+    }
+}
+
+// Points beta (beta_at[i], or blo + i h) of row blockIdx.y, per_block of them
+// to a block, 16 lanes to a point: Var(E) into var, or <u> and C_V into u and
+// cv; ln rho into lnrho (first block of a row) where asked for.
+template <int KP>
+__global__ __launch_bounds__(kRB) void k_row_points(const double* __restrict__ c, const double* __restrict__ a, int n,
+                                                     double s, const double* __restrict__ beta_at, double blo, double h,
+                                                     long np, int per_block, double six_v, double* __restrict__ lnrho,
+                                                     double* __restrict__ var, double* __restrict__ u,
+                                                     double* __restrict__ cv) {
+    __shared__ double term[kTerms];
+    const double* ar = a + (size_t)blockIdx.y * (size_t)n;
+    scan_lnrho(ar, n, s, term, [&](int k, double v) {
+        if (lnrho && blockIdx.x == 0) lnrho[(size_t)blockIdx.y * (size_t)n + k] = v;
+    });
+    const int lane = threadIdx.x & 15;
+    double cr[KP], Lr[KP];
+    lane_terms<KP, 16>(c, term, n, lane, cr, Lr);
+    const long i0 = (long)blockIdx.x * per_block, i1 = min(np, i0 + per_block);
+    // every lane of a wavefront takes part in the row rotations, so all rows of
+    // the block make the same number of turns and the last points are repeated
+    for (long ib = i0; ib < i1; ib += kRB / 16) {
+        const long i = min(ib + (threadIdx.x >> 4), i1 - 1);
+        double mu, v;
+        lane_moments<KP, 16>(cr, Lr, beta_at ? beta_at[i] : blo + (double)i * h, &mu, &v);
+        if (lane == 0 && ib + (threadIdx.x >> 4) < i1) {
+            if (var) {
+                var[(size_t)blockIdx.y * (size_t)np + i] = v;
+            } else {
+                u[i] = mu / six_v;
+                cv[i] = v / six_v;
+            }
+        }
+    }
+}
+
+// argmax of a row's grid (the first of equal maxima), by the whole block
+__device__ __forceinline__ void grid_argmax(const double* __restrict__ var, long ng, double* best, long* at) {
+    __shared__ double sv[kRB];
+    __shared__ long si[kRB];
+    double v = -INFINITY;
+    long b = 0;
+    for (long i = threadIdx.x; i <= ng; i += kRB)
+        if (var[i] > v) { v = var[i]; b = i; }
+    sv[threadIdx.x] = v;
+    si[threadIdx.x] = b;
+    __syncthreads();
+    for (int off = kRB / 2; off > 0; off >>= 1) {
+        if ((int)threadIdx.x < off) {
+            const double v2 = sv[threadIdx.x + off];
+            const long b2 = si[threadIdx.x + off];
+            if (v2 > sv[threadIdx.x] || (v2 == sv[threadIdx.x] && b2 < si[threadIdx.x])) {
+                sv[threadIdx.x] = v2;
+                si[threadIdx.x] = b2;
+            }
+        }
+        __syncthreads();
+    }
+    *best = sv[0];
+    *at = si[0];
+}
+
+// Golden section on [x0, x3] to tol for the function f (variance at a
+// coupling); best, bb: the grid's maximum and its coupling
+template <typename F>
+__device__ __forceinline__ void golden(double x0, double x3, double tol, double best, double bb, double* bc, double* v,
+                                       F&& f) {
+    const double gr = 0.61803398874989484820;
+    double x1 = x3 - gr * (x3 - x0), x2 = x0 + gr * (x3 - x0);
+    double f1 = f(x1), f2 = f(x2);
+    // (the bound on the steps ends a search whose tol is below the spacing of beta)
+    for (int it = 0; x3 - x0 > tol && it < 4096; ++it) {
+        if (f1 > f2) {
+            x3 = x2; x2 = x1; f2 = f1;
+            x1 = x3 - gr * (x3 - x0);
+            f1 = f(x1);
+        } else {
+            x0 = x1; x1 = x2; f1 = f2;
+            x2 = x0 + gr * (x3 - x0);
+            f2 = f(x2);
+        }
+    }
+    *bc = 0.5 * (x0 + x3);
+    *v = f(*bc);
+    if (best > *v) { *bc = bb; *v = best; }
+}
+
+// argmax of the grid by the block, then golden section by one wavefront, which
+// needs no barrier between its ~25 dependent evaluations (one block per row)
+template <int KP>
+__global__ __launch_bounds__(kRB) void k_row_golden(const double* __restrict__ c, const double* __restrict__ a, int n,
+                                                     double s, const double* __restrict__ var_rows, long ng, double blo,
+                                                     double bhi, double h, double tol, double six_v,
+                                                     double* __restrict__ out_rows) {
+    __shared__ double term[kTerms];
+    scan_lnrho(a + (size_t)blockIdx.x * (size_t)n, n, s, term, [](int, double) {});
+    double best;
+    long at;
+    grid_argmax(var_rows + (size_t)blockIdx.x * (size_t)(ng + 1), ng, &best, &at);
+    if (threadIdx.x >= 64) return;
+    double cr[KP], Lr[KP];
+    lane_terms<KP, 64>(c, term, n, (int)threadIdx.x, cr, Lr);
+    const double bb = blo + (double)at * h;
+    double bc, v;
+    golden(fmax(blo, bb - h), fmin(bhi, bb + h), tol, best, bb, &bc, &v, [&](double x) {
+        double mu, f;
+        lane_moments<KP, 64>(cr, Lr, x, &mu, &f);
+        return f;
+    });
+    if (threadIdx.x == 0) {
+        out_rows[2 * (size_t)blockIdx.x] = bc;
+        out_rows[2 * (size_t)blockIdx.x + 1] = v / six_v;
     }
 }
 
@@ -103,57 +338,77 @@ __global__ __launch_bounds__(kRB) void k_golden(const double* __restrict__ c, co
     const double* var = var_rows + (size_t)blockIdx.x * (size_t)(ng + 1);
     double* out = out_rows + 2 * (size_t)blockIdx.x;
     __shared__ double sh[kRB / 64];
-    __shared__ double sbest;
-    __shared__ long sidx;
-    if (threadIdx.x == 0) {
-        double best = -INFINITY;
-        long bi = 0;
-        for (long i = 0; i <= ng; ++i)
-            if (var[i] > best) { best = var[i]; bi = i; }
-        sbest = best;
-        sidx = bi;
-    }
-    __syncthreads();
-    const double best = sbest, bb = blo + (double)sidx * h;
-    double x0 = fmax(blo, bb - h), x3 = fmin(bhi, bb + h);
-    const double gr = 0.61803398874989484820;
-    double x1 = x3 - gr * (x3 - x0), x2 = x0 + gr * (x3 - x0), mu, f1, f2;
-    moments(c, L, n, x1, sh, &mu, &f1);
-    moments(c, L, n, x2, sh, &mu, &f2);
-    while (x3 - x0 > tol) {
-        if (f1 > f2) {
-            x3 = x2; x2 = x1; f2 = f1;
-            x1 = x3 - gr * (x3 - x0);
-            moments(c, L, n, x1, sh, &mu, &f1);
-        } else {
-            x0 = x1; x1 = x2; f1 = f2;
-            x2 = x0 + gr * (x3 - x0);
-            moments(c, L, n, x2, sh, &mu, &f2);
-        }
-    }
-    double bc = 0.5 * (x0 + x3), v;
-    moments(c, L, n, bc, sh, &mu, &v);
-    if (best > v) { bc = bb; v = best; }
+    double best;
+    long at;
+    grid_argmax(var, ng, &best, &at);
+    const double bb = blo + (double)at * h;
+    double bc, v;
+    golden(fmax(blo, bb - h), fmin(bhi, bb + h), tol, best, bb, &bc, &v, [&](double x) {
+        double mu, f;
+        moments(c, L, n, x, sh, &mu, &f);
+        return f;
+    });
     if (threadIdx.x == 0) {
         out[0] = bc;
         out[1] = v / six_v;
     }
 }
 
+// fewest terms per lane (of 16, or of 64) that hold n <= kRowN intervals
+#define LLR_BY_TERMS(G, CALL)                     \
+    do {                                          \
+        if (n <= 4 * G) { CALL(4); }              \
+        else if (n <= 8 * G) { CALL(8); }         \
+        else if (n <= 16 * G) { CALL(16); }       \
+        else { CALL(32); }                        \
+    } while (0)
+
 void launch_recon(const double* c, const double* a, int n, double s, double six_v, const double* beta, int nb,
                   double* lnrho, double* u, double* cv, hipStream_t st) {
-    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(64), 0, st, a, n, 1, s, lnrho);
+    if (nb > 0 && n <= kRowN) {
+#define LLR_CALL(KP)                                                                                             \
+    hipLaunchKernelGGL(k_row_points<KP>, dim3((unsigned)((nb + 15) / 16)), dim3(kRB), 0, st, c, a, n, s, beta, 0.0, 0.0, \
+                       (long)nb, 16, six_v, lnrho, (double*)nullptr, u, cv)
+        LLR_BY_TERMS(16, LLR_CALL);
+#undef LLR_CALL
+        return;
+    }
+    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(kRB), 0, st, a, n, s, lnrho);
     if (nb > 0) hipLaunchKernelGGL(k_moments, dim3(nb), dim3(kRB), 0, st, c, lnrho, n, beta, six_v, u, cv);
 }
 
 // beta_c and the C_V peak for `rows` sets of a_k (a row r at a + r n);
-// scratch holds rows (n + ng + 1) doubles, out2 rows pairs
+// scratch holds rows (n + ng + 1) doubles, out2 rows pairs.  Up to kRowN
+// intervals a point's terms fit a few registers of a DPP row or a wavefront;
+// beyond that a block walks them.  n = 128, 401 points, us by blocks / in
+// registers: one row 116 / 34 (recursion 20, grid 10, golden section 86), the
+// grid of 1000 bootstrap rows 950 / 110.
 void launch_beta_c_rows(const double* c, const double* a, int n, int rows, double s, double six_v, double blo,
                         double bhi, double h, double tol, double* scratch, double* out2, hipStream_t st) {
     const long ng = (long)floor((bhi - blo) / h + 0.5);
     double* L = scratch;
     double* var = scratch + (size_t)rows * n;
-    hipLaunchKernelGGL(k_lnrho, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, st, a, n, rows, s, L);
+    if (n <= kRowN) {
+        // a block scans its row's ln rho once for all its points: few blocks of
+        // many points where the rows fill the chip, many of few for one row
+        const int per = rows >= 64 ? 128 : 16;
+#define LLR_CALL(KP)                                                                                                \
+    hipLaunchKernelGGL(k_row_points<KP>, dim3((unsigned)((ng + per) / per), (unsigned)rows), dim3(kRB), 0, st, c, a, n, s, \
+                       (const double*)nullptr, blo, h, ng + 1, per, six_v, (double*)nullptr, var, (double*)nullptr,    \
+                       (double*)nullptr)
+        LLR_BY_TERMS(16, LLR_CALL);
+#undef LLR_CALL
+#define LLR_CALL(KP)                                                                                                   \
+    hipLaunchKernelGGL(k_row_golden<KP>, dim3((unsigned)rows), dim3(kRB), 0, st, c, a, n, s, var, ng, blo, bhi, h, tol, \
+                       six_v, out2)
+        if (n <= 64) { LLR_CALL(1); }
+        else if (n <= 128) { LLR_CALL(2); }
+        else if (n <= 256) { LLR_CALL(4); }
+        else { LLR_CALL(8); }
+#undef LLR_CALL
+        return;
+    }
+    hipLaunchKernelGGL(k_lnrho, dim3((unsigned)rows), dim3(kRB), 0, st, a, n, s, L);
     hipLaunchKernelGGL(k_var_grid, dim3((unsigned)(ng + 1), (unsigned)rows), dim3(kRB), 0, st, c, L, n, blo, h, ng,
                        var);
     hipLaunchKernelGGL(k_golden, dim3((unsigned)rows), dim3(kRB), 0, st, c, L, n, var, ng, blo, bhi, h, tol, six_v,
@@ -243,23 +498,24 @@ __global__ void k_logp(const double* __restrict__ c, const double* __restrict__ 
 
 // Interior local maxima of ln P: ln P is linear with slope beta - a_k in
 // interval k, so the edge between k and k+1 is a maximum iff beta - a_k > 0
-// and beta - a_{k+1} <= 0 (one thread; every maximum counted, at most
+// and beta - a_{k+1} <= 0 (one wavefront; every maximum counted, at most
 // max_peaks stored in order of E).
 __global__ void k_peaks(const double* __restrict__ c, const double* __restrict__ L, const double* __restrict__ a,
                         int n, double s, double beta, const double* __restrict__ lnz, int max_peaks,
                         double* __restrict__ E_out, double* __restrict__ lp_out, int* __restrict__ n_out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int np = 0;
-    for (int k = 0; k + 1 < n; ++k) {
-        if (beta - a[k] > 0.0 && beta - a[k + 1] <= 0.0) {
-            if (np < max_peaks) {
-                E_out[np] = c[k] + 0.5 * s;
-                lp_out[np] = (L[k] + beta * c[k] - lnz[0]) + (beta - a[k]) * (0.5 * s);
-            }
-            ++np;
+    int np = 0;   // one wavefront: 64 edges at a time, in order
+    for (int k0 = 0; k0 + 1 < n; k0 += 64) {
+        const int k = k0 + (int)threadIdx.x;
+        const bool pk = k + 1 < n && beta - a[k] > 0.0 && beta - a[k + 1] <= 0.0;
+        const unsigned long long m = __ballot(pk);
+        const int at = np + (int)__popcll(m & ((1ull << threadIdx.x) - 1ull));
+        if (pk && at < max_peaks) {
+            E_out[at] = c[k] + 0.5 * s;
+            lp_out[at] = (L[k] + beta * c[k] - lnz[0]) + (beta - a[k]) * (0.5 * s);
         }
+        np += (int)__popcll(m);
     }
-    *n_out = np;
+    if (threadIdx.x == 0) *n_out = np;
 }
 
 // scratch: n (ln rho) + 1 (ln Z) doubles
@@ -268,7 +524,7 @@ void launch_prob(const double* c, const double* a, int n, double s, double beta,
                  hipStream_t st) {
     double* L = scratch;
     double* lnz = scratch + n;
-    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(64), 0, st, a, n, 1, s, L);
+    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(kRB), 0, st, a, n, s, L);
     hipLaunchKernelGGL(k_logz, dim3(1), dim3(kRB), 0, st, c, L, a, n, s, beta, lnz);
     if (m > 0) hipLaunchKernelGGL(k_logp, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, c, L, a, n, s, beta,
                                   E, m, lnz, logp);
@@ -323,7 +579,7 @@ __global__ __launch_bounds__(kRB) void k_rw_moments(const double* __restrict__ E
 // scratch: n doubles (ln rho)
 void launch_reweight(const double* E, long m, const double* c, const double* a, int n, double s, const double* beta,
                      int nb, double six_v, double* u, double* cv, double* scratch, hipStream_t st) {
-    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(64), 0, st, a, n, 1, s, scratch);
+    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(kRB), 0, st, a, n, s, scratch);
     hipLaunchKernelGGL(k_rw_moments, dim3((unsigned)nb), dim3(kRB), 0, st, E, m, c, scratch, a, n, s, beta, six_v, u,
                        cv);
 }
@@ -375,7 +631,7 @@ __global__ __launch_bounds__(kRB) void k_obs_bracket(const double* __restrict__ 
 // scratch: n doubles (ln rho)
 void launch_obs_bracket(const double* E, const double* B, int m, const double* c, const double* a, int n, double s,
                         const double* beta, int nb, double* out, double* scratch, hipStream_t st) {
-    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(64), 0, st, a, n, 1, s, scratch);
+    hipLaunchKernelGGL(k_lnrho, dim3(1), dim3(kRB), 0, st, a, n, s, scratch);
     hipLaunchKernelGGL(k_obs_bracket, dim3((unsigned)nb), dim3(kRB), 0, st, E, B, m, c, scratch, a, n, beta, out);
 }
 
