@@ -166,6 +166,9 @@ static llr_status dalloc(llr_ctx* c, P** p, size_t count) {
 // ceil(2^32 / d) for d >= 2 (divisor 1 is handled by the kernels directly)
 static uint32_t magic(uint32_t d) { return d < 2 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
 
+// floor(2^32 / d), at most 2^32 - 1
+static uint32_t reciprocal(int d) { return (uint32_t)std::min<unsigned long long>(0xffffffffull, (1ull << 32) / (unsigned)d); }
+
 static double restriction_width(const llr_ctx* c, double dE) {
     return c->prm.replica_exchange ? (1.0 + c->prm.overlap) * dE : dE;
 }
@@ -209,6 +212,9 @@ static void set_tiles(LatTable& lt, int hb_lpt, int or_lpt) {
         // ceil(L / LPT) groups of consecutive x3
         d.hb_bpc = d.npt * ((d.L + hb_lpt - 1) / hb_lpt);
         d.or_bpc = d.npt * ((d.L + or_lpt - 1) / or_lpt);
+        d.m_npt = reciprocal(d.npt);
+        d.m_hb = reciprocal(d.hb_bpc);
+        d.m_or = reciprocal(d.or_bpc);
         d.hb_block0 = hb0;
         d.or_block0 = or0;
         hb0 += d.n_chains * d.hb_bpc;

@@ -21,26 +21,6 @@
 
 namespace llr {
 
-// Sum over the wavefront (the order does not matter for integers): DPP row
-// shifts and broadcasts instead of twelve cross-lane LDS permutes.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ long long dpp_add(long long v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, ROWS, 0xf, false);
-    return v + (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ long long wave_sum_i64(long long v) {
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its sum
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the sum
-    const int lo = __builtin_amdgcn_readlane((int)v, 63);
-    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), 63);
-    return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
 __device__ __forceinline__ int lanes_below(unsigned long long m) {
     return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
@@ -304,12 +284,7 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                         T q, rm1, kg2;
                         vm_constants(ak[r], q, rm1, kg2);
                         const uint4 w = philox10(make_uint4((uint32_t)(r * NT + tid), c1base, sweep, c3), a.k0, a.k1);
-                        if (ak[r] == T(0)) {
-                            M::sincos_halfpi_w(w.x, &sh[r], &ch[r]);
-                        } else {
-                            got[r] = vm_attempt(w.x, w.y, q, rm1, kg2, ch[r], sh[r]);
-                            if (!got[r]) got[r] = vm_attempt(w.z, w.w, q, rm1, kg2, ch[r], sh[r]);
-                        }
+                        got[r] = vm_first_two(w, ak[r], q, rm1, kg2, ch[r], sh[r]);
                     }
                 }
                 chain_tail<T, LPT>(got, ch, sh, ak, k, w_h[wid], w_ak[wid], c1base, sweep, c3, a.k0, a.k1);
@@ -327,8 +302,8 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                     if constexpr (M::f32) fx32 += __float2int_rn(dE * 33554432.0f);
                     else fx += to_fixed((double)dE, L);
                 }
-                if constexpr (M::f32) fx = (long long)fx32 << (L.fxb - 25);
-                fx = wave_sum_i64(fx);
+                if constexpr (M::f32) fx = wave_sum_i32(fx32) << (L.fxb - 25);
+                else fx = wave_sum_i64(fx);
                 if (lane == 0) part[flip][wid] = fx;
                 __syncthreads();   // also: every thread has read its staples
                 long long total = 0;

@@ -109,6 +109,7 @@ template <> struct Math<double> {
     }
     __device__ static __forceinline__ double atan2_(double y, double x) { return atan2(y, x); }
     __device__ static __forceinline__ double sqrt_(double x) { return sqrt(x); }
+    __device__ static __forceinline__ double abs_(double x) { return fabs(x); }
     __device__ static __forceinline__ double log_(double x) { return log(x); }
     __device__ static __forceinline__ double div_(double a, double b) { return a / b; }
     __device__ static __forceinline__ double pi() { return 3.14159265358979323846; }
@@ -166,6 +167,7 @@ template <> struct Math<float> {
         return y < 0.f ? -r : r;
     }
     __device__ static __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
+    __device__ static __forceinline__ float abs_(float x) { return __builtin_fabsf(x); }
     __device__ static __forceinline__ float log_(float x) { return __logf(x); }
     __device__ static __forceinline__ float div_(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
     __device__ static __forceinline__ float pi() { return 3.14159265f; }
@@ -187,6 +189,19 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     const int per = nb >> 3, rem = nb & 7;
     const int xcd = b & 7, idx = b >> 3;
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
+}
+
+// n / d and its remainder for 0 <= n < 2^31 with m = floor(2^32 / d) (2^32 - 1 for
+// d = 1): the estimate is at most one too small.  On uniform values this is scalar
+// work, where the compiler's division goes through the vector unit.
+__device__ __forceinline__ int udiv(int n, int d, uint32_t m, int& rem) {
+    int q = (int)__umulhi((uint32_t)n, m);
+    rem = n - q * d;
+    if (rem >= d) {
+        rem -= d;
+        ++q;
+    }
+    return q;
 }
 
 // exact n / d for n < 2^32 / d via a precomputed m = ceil(2^32 / d)

@@ -22,6 +22,7 @@ struct LatDev {
     int or_bpc, or_block0; // overrelaxation pass: the same
     uint32_t P;            // positions in the (x0h, x1, x2) slab: hL L^2 = V/(2L); h = pos + P x3
     int npt;               // position tiles of kBlock per slab, ceil(P / kBlock)
+    uint32_t m_npt, m_hb, m_or;   // udiv's reciprocals of npt, hb_bpc, or_bpc
     int ebpc;              // blocks per chain in the site kernels (2 x V/2 / 256, rounded up)
     int hstr[4];           // half-index stride of a step along nu = 1..3: (L/2) L^(nu-1); [0] unused
     int hwrap[4];          // (L - 1) hstr[nu]: the periodic jump across the boundary

@@ -15,56 +15,126 @@ namespace llr {
 // accepted, no counters touched; the walk kernel then decides)
 enum { kModeRestricted = 0, kModeApproach = 1, kModeFree = 2, kModeMuca = 3, kModeLink = 4,
        kModeTune = kHbModeTune, kModeLinkPre = 6 };
+// Whether a condition that almost never holds does so on any lane: one compare
+// and a scalar branch, where a select would cost every lane an instruction per
+// value and a divergent branch the copies of its merge.
+__device__ __forceinline__ bool any_lane(bool c) { return __builtin_expect(__ballot(c) != 0ull, 0); }
+
 // Best-Fisher constants in the cancellation-free form: q = (1-rho)/(1+rho),
 // r - 1 = (1-rho)^2/(2 rho), kappa (r^2 - 1) with sqrt(r^2-1) = (1-rho^2)/(2 rho).
 template <typename T>
 __device__ __forceinline__ void vm_constants(T ak, T& q, T& rm1, T& kg2) {
     using M = Math<T>;
-    q = T(1); rm1 = T(1); kg2 = T(0);
-    if (ak > T(0)) {
-        // rho = 2 ak / D with D = tau + sqrt(2 tau); in terms of D:
-        // q = (D - 2ak)/(D + 2ak), (1-rho)^2/(2 rho) = (D - 2ak)^2/(4 ak D),
-        // (1-rho^2)/(2 rho) = (D - 2ak)(D + 2ak)/(4 ak D)
-        const T tau = T(1) + M::sqrt_(T(1) + T(4) * ak * ak);
-        const T D = tau + M::sqrt_(T(2) * tau);
-        const T dm = D - T(2) * ak, dp = D + T(2) * ak;
-        if constexpr (M::f32) {
-            // 1/(4 ak D) and 1/dp from one reciprocal of their product
-            const T fd = T(4) * ak * D;
-            const T t = M::div_(T(1), fd * dp);
-            const T r1 = dp * t;
-            rm1 = dm * dm * r1;
-            const T gg = dm * dp * r1;
-            kg2 = ak * gg * gg;
-            q = dm * (fd * t);
-        } else {
-            const T r1 = M::div_(T(1), T(4) * ak * D);
-            rm1 = dm * dm * r1;
-            const T gg = dm * dp * r1;
-            kg2 = ak * gg * gg;
-            q = M::div_(dm, dp);
+    // rho = 2 ak / D with D = tau + sqrt(2 tau); in terms of D:
+    // q = (D - 2ak)/(D + 2ak), (1-rho)^2/(2 rho) = (D - 2ak)^2/(4 ak D),
+    // (1-rho^2)/(2 rho) = (D - 2ak)(D + 2ak)/(4 ak D)
+    const T tau = T(1) + M::sqrt_(T(1) + T(4) * ak * ak);
+    const T D = tau + M::sqrt_(T(2) * tau);
+    const T dm = D - T(2) * ak, dp = D + T(2) * ak;
+    if constexpr (M::f32) {
+        // 1/(4 ak D) and 1/dp from one reciprocal of their product
+        const T fd = T(4) * ak * D;
+        const T t = M::div_(T(1), fd * dp);
+        const T r1 = dp * t;
+        rm1 = dm * dm * r1;
+        const T gg = dm * dp * r1;
+        kg2 = ak * gg * gg;
+        q = dm * (fd * t);
+    } else {
+        const T r1 = M::div_(T(1), T(4) * ak * D);
+        rm1 = dm * dm * r1;
+        const T gg = dm * dp * r1;
+        kg2 = ak * gg * gg;
+        q = M::div_(dm, dp);
+    }
+    if (any_lane(!(ak > T(0)))) {   // no coupling: a uniform angle
+        if (!(ak > T(0))) {
+            q = T(1);
+            rm1 = T(1);
+            kg2 = T(0);
         }
     }
 }
 
 // One sampler attempt from the word pair (wa, wb): accept test of Best &
-// Fisher with z = cos(pi V1); on accept (ch, sh) = (cos, q sin)(pi V1 / 2).
+// Fisher with z = cos(pi V1); (c_, s_) = (cos, q sin)(pi V1 / 2).  Both accept
+// tests are always evaluated: on nearly every wavefront some lane needs the
+// second.
 template <typename T>
-__device__ __forceinline__ bool vm_attempt(uint32_t wa, uint32_t wb, T q, T rm1, T kg2, T& ch, T& sh) {
+__device__ __forceinline__ bool vm_try(uint32_t wa, uint32_t wb, T q, T rm1, T kg2, T& c_, T& s_) {
     using M = Math<T>;
-    T s_, c_;
     M::sincos_halfpi_w(wa, &s_, &c_);
+    s_ = q * s_;
     const T U2 = M::unif(wb);
     const T cc = M::div_(kg2, M::fma_(T(2) * c_, c_, rm1));   // kappa (r^2 - 1)/(r + z)
-    bool acc = M::fma_(cc, T(2) - cc, -U2) > T(0);
+    const bool squeeze = M::fma_(cc, T(2) - cc, -U2) > T(0);
+    bool full;
     if constexpr (M::f32) {
         // ln(c/U2) + 1 - c >= 0 as c >= U2 e^(c - 1): one transcendental
-        if (!acc) acc = cc >= U2 * __builtin_amdgcn_exp2f(M::fma_(cc, 1.44269504088896341f, -1.44269504088896341f));
+        full = cc >= U2 * __builtin_amdgcn_exp2f(M::fma_(cc, 1.44269504088896341f, -1.44269504088896341f));
     } else {
-        if (!acc) acc = M::log_(M::div_(cc, U2)) + T(1) - cc >= T(0);
+        full = M::log_(M::div_(cc, U2)) + T(1) - cc >= T(0);
     }
-    if (acc) { ch = c_; sh = q * s_; }
+    return squeeze | full;
+}
+// The same, writing (ch, sh) only on acceptance.
+template <typename T>
+__device__ __forceinline__ bool vm_attempt(uint32_t wa, uint32_t wb, T q, T rm1, T kg2, T& ch, T& sh) {
+    T c_, s_;
+    const bool acc = vm_try(wa, wb, q, rm1, kg2, c_, s_);
+    ch = acc ? c_ : ch;
+    sh = acc ? s_ : sh;
     return acc;
+}
+// Attempts 0 and 1 of a link from one Philox call: the first accepted one's
+// (ch, sh).  Both are evaluated, since on nearly every wavefront some lane needs
+// the second.  A link without coupling takes attempt 0 (its q is 1).
+template <typename T>
+__device__ __forceinline__ bool vm_first_two(const uint4& w, T ak, T q, T rm1, T kg2, T& ch, T& sh) {
+    T c1, s1;
+    const bool a0 = vm_try(w.x, w.y, q, rm1, kg2, ch, sh);
+    const bool a1 = vm_try(w.z, w.w, q, rm1, kg2, c1, s1);
+    const bool keep = a0 | (ak == T(0));
+    ch = keep ? ch : c1;
+    sh = keep ? sh : s1;
+    return keep | a1;
+}
+
+// Sum over the wavefront (the order does not matter for integers): DPP row
+// shifts and broadcasts instead of twelve cross-lane LDS permutes.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_add(long long v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, ROWS, 0xf, false);
+    return v + (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ long long wave_sum_i64(long long v) {
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its sum
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the sum
+    const int lo = __builtin_amdgcn_readlane((int)v, 63);
+    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), 63);
+    return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+// The same for 32-bit values: their 16-bit halves add up without overflow, and
+// each step is one instruction with a DPP operand.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add32(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+__device__ __forceinline__ int wave_sum_small(int v) {
+    v = dpp_add32<0x111, 0xf>(v);
+    v = dpp_add32<0x112, 0xf>(v);
+    v = dpp_add32<0x114, 0xf>(v);
+    v = dpp_add32<0x118, 0xf>(v);
+    v = dpp_add32<0x142, 0xa>(v);
+    v = dpp_add32<0x143, 0xc>(v);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ long long wave_sum_i32(int v) {
+    return ((long long)wave_sum_small(v >> 16) << 16) + (long long)wave_sum_small(v & 0xffff);
 }
 
 // A link's Delta E in the lattice's fixed point 2^-fxb (FP64 path).  The FP32
@@ -94,9 +164,15 @@ __device__ __forceinline__ void hb_new_angle(T c_, T s_, T C, T S, T R, T kap, T
     using M = Math<T>;
     T er = fms2(c_, c_, s_, s_), ei = T(2) * c_ * s_;
     const T nrm = fma2(c_, c_, s_, s_);
-    if (kap < T(0)) { er = -er; ei = -ei; }
+    if (any_lane(kap < T(0))) {
+        er = kap < T(0) ? -er : er;
+        ei = kap < T(0) ? -ei : ei;
+    }
     T pr = C, pi = -S;
-    if (R == T(0)) { pr = T(1); pi = T(0); }
+    if (any_lane(R == T(0))) {
+        pr = R == T(0) ? T(1) : pr;
+        pi = R == T(0) ? T(0) : pi;
+    }
     const T zr = fms2(er, pr, ei, pi), zi = fma2(er, pi, ei, pr);
     t_new = M::atan2_(zi, zr);
     if (!M::f32 && t_new >= M::pi()) t_new -= T(2) * M::pi();
@@ -112,9 +188,15 @@ __device__ __forceinline__ void hb_or_new_angle(T c_, T s_, T C, T S, T R, T kap
     using M = Math<T>;
     T er = fms2(c_, c_, s_, s_), ei = T(2) * c_ * s_;
     const T nrm = fma2(c_, c_, s_, s_);
-    if (kap < T(0)) { er = -er; ei = -ei; }
+    if (any_lane(kap < T(0))) {
+        er = kap < T(0) ? -er : er;
+        ei = kap < T(0) ? -ei : ei;
+    }
     T pr = C, pi = -S;
-    if (R == T(0)) { pr = T(1); pi = T(0); }
+    if (any_lane(R == T(0))) {
+        pr = R == T(0) ? T(1) : pr;
+        pi = R == T(0) ? T(0) : pi;
+    }
     const T zr = fma2(er, pr, ei, pi), zi = fms2(er, pi, ei, pr);   // (er - i ei)(pr + i pi)
     t_or = M::atan2_(zi, zr);
     if (!M::f32 && t_or >= M::pi()) t_or -= T(2) * M::pi();
@@ -127,15 +209,11 @@ __device__ __forceinline__ void hb_or_new_angle(T c_, T s_, T C, T S, T R, T kap
 template <typename T>
 __device__ __forceinline__ T or_angle_sc(T t, T so, T co, T C, T S) {
     using M = Math<T>;
-    T t_new;
-    if (C == T(0) && S == T(0)) {
-        t_new = -t;
-    } else {
-        const T ar = fms2(C, C, S, S), ai = T(-2) * C * S;   // (C - iS)^2
-        const T zr = fma2(ar, co, ai, so);                   // times (cos - i sin)
-        const T zi = fms2(ai, co, ar, so);
-        t_new = M::atan2_(zi, zr);
-    }
+    const T ar = fms2(C, C, S, S), ai = T(-2) * C * S;   // (C - iS)^2
+    const T zr = fma2(ar, co, ai, so);                   // times (cos - i sin)
+    const T zi = fms2(ai, co, ar, so);
+    T t_new = M::atan2_(zi, zr);
+    if (any_lane(C == T(0) && S == T(0))) t_new = C == T(0) && S == T(0) ? -t : t_new;
     if (!M::f32 && t_new >= M::pi()) t_new -= T(2) * M::pi();
     return t_new;
 }

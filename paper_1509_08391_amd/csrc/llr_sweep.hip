@@ -23,6 +23,9 @@ namespace llr {
 // instantiations of the heatbath class pass
 enum { kHbPlain = 0, kHbPre = 1, kHbFuseOr = 2 };
 
+// links whose loads are in flight while one link's staples are summed
+constexpr int kHbAhead = 1, kOrAhead = 1;
+
 constexpr long long kLinkNone = (long long)0x8000000000000000ull;   // no free candidate within the cap
 
 __device__ __forceinline__ int find_lat_site(const LatTable& lt, int b) {
@@ -61,8 +64,8 @@ struct ColTile {
 template <int LPT>
 __device__ __forceinline__ ColTile col_tile(const LatDev& L, int tile, int tid) {
     ColTile t;
-    const int xg = tile / L.npt;
-    const int pt = tile - xg * L.npt;
+    int pt;
+    const int xg = udiv(tile, L.npt, L.m_npt, pt);
     t.pos0 = (uint32_t)pt * kBlock;
     const uint32_t pos = t.pos0 + (uint32_t)tid;
     t.in_slab = pos < L.P;
@@ -121,30 +124,62 @@ __device__ __forceinline__ void neighbour_offsets(const LatDev& L, const int x[4
     }
 }
 
-// Neighbour offsets of a thread's column (see col_tile), split into a
-// per-lane part along x0, x1, x2 and a wavefront-uniform part along x3:
-//   v_up[d], v_dn[d] (d < 3): half-index offsets of x +- d within the slab,
-//   for the thread's links with x0 = 2 x0h + b[k], k = r & 1 (the parity of
-//   x0 alternates along the column); v_up[3] = v_dn[3] = 0;
-//   the offsets along x3 and the link's own shift P x3 are uniform and are
-//   added to the plane's base address.
+// A chain's 2 x 8 planes as one buffer resource.  An access is then base + lane
+// offset + uniform offset with the uniform part (plane, x3 and a step along x3)
+// in one scalar register: the lane offsets are computed once per column, a load
+// costs one scalar add, and an address outside the chain is not accessed.
+template <typename T>
+struct ChainBuf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ ChainBuf(T* chain, uint32_t V2)
+        : r(__builtin_amdgcn_make_buffer_rsrc((void*)chain, 0, (int)(16u * V2 * (uint32_t)sizeof(T)), 0x00027000)) {}
+    __device__ __forceinline__ T load(uint32_t lane, uint32_t uni) const {
+        if constexpr (sizeof(T) == 4) {
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)lane, (int)uni, 0));
+        } else {
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane, (int)uni, 0));
+        }
+    }
+    __device__ __forceinline__ void store(uint32_t lane, uint32_t uni, T v) const {
+        if constexpr (sizeof(T) == 4) {
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, (int)lane, (int)uni, 0);
+        } else {
+            typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)lane, (int)uni, 0);
+        }
+    }
+};
+
+// Byte offset in the chain of colour c's current plane (other: the non-current)
+template <typename T>
+__device__ __forceinline__ uint32_t plane_off(uint64_t curw, int c, uint32_t V2, int other = 0) {
+    return ((uint32_t)(((curw >> (8 * c)) & 1ull) ^ (uint64_t)other) * 8u + (uint32_t)c) * V2 * (uint32_t)sizeof(T);
+}
+
+// Lane byte offsets of a thread's column within a slab (see col_tile): its own
+// position and the steps along x0, x1, x2.  The links' x0 = 2 x0h + b alternates
+// in parity along the column, so the x0 steps come in two versions, for the
+// column's even and odd links; the steps along x3 and the link's own shift P x3
+// are uniform.
 struct ColNbr {
-    int up0[2], dn0[2];   // along x0 for the column's even / odd links
+    uint32_t pos;
+    int up0[2], dn0[2];
     int up1, dn1, up2, dn2;
 };
-__device__ __forceinline__ ColNbr col_nbr(const LatDev& L, const ColTile& t, int p) {
+__device__ __forceinline__ ColNbr col_nbr(const LatDev& L, const ColTile& t, int p, int esz) {
     ColNbr n;
     const int b0 = (p + t.x1 + t.x2 + t.x3_0) & 1;   // x0 = 2 x0h + b0 for the even links
-    const int uo = t.x0h == L.hL - 1 ? 1 - L.hL : 1;  // x0 odd: the partner site 2 x0h + 2 (periodic)
-    const int de = t.x0h == 0 ? L.hL - 1 : -1;        // x0 even: the partner site 2 x0h - 1 (periodic)
+    const int uo = (t.x0h == L.hL - 1 ? 1 - L.hL : 1) * esz;  // x0 odd: the partner site 2 x0h + 2 (periodic)
+    const int de = (t.x0h == 0 ? L.hL - 1 : -1) * esz;        // x0 even: the partner site 2 x0h - 1 (periodic)
+    n.pos = t.pos * (uint32_t)esz;
     n.up0[0] = b0 ? uo : 0;
     n.dn0[0] = b0 ? 0 : de;
     n.up0[1] = b0 ? 0 : uo;
     n.dn0[1] = b0 ? de : 0;
-    n.up1 = t.x1 == L.L - 1 ? -L.hwrap[1] : L.hstr[1];
-    n.dn1 = t.x1 == 0 ? L.hwrap[1] : -L.hstr[1];
-    n.up2 = t.x2 == L.L - 1 ? -L.hwrap[2] : L.hstr[2];
-    n.dn2 = t.x2 == 0 ? L.hwrap[2] : -L.hstr[2];
+    n.up1 = (t.x1 == L.L - 1 ? -L.hwrap[1] : L.hstr[1]) * esz;
+    n.dn1 = (t.x1 == 0 ? L.hwrap[1] : -L.hstr[1]) * esz;
+    n.up2 = (t.x2 == L.L - 1 ? -L.hwrap[2] : L.hstr[2]) * esz;
+    n.dn2 = (t.x2 == 0 ? L.hwrap[2] : -L.hstr[2]) * esz;
     return n;
 }
 
@@ -153,46 +188,65 @@ __device__ __forceinline__ ColNbr col_nbr(const LatDev& L, const ColTile& t, int
 //   forward  s_f = th_nu(x+mu) - th_mu(x+nu) - th_nu(x)
 //   backward s_b = th_nu(x-nu) - th_nu(x+mu-nu) - th_mu(x-nu)
 // C + i S = sum of e^{i s}.  The link sits at slab position pos (per lane) and
-// x3 = x3 (uniform); K = x3 parity relative to the column's first link selects
-// the x0 offsets.  Every neighbour's half index is pos + (per-lane offset
-// along x0..x2) + (uniform: P x3 and the offset along x3).
-// UB: the uniform part of every index goes into the plane's base address (a
-// scalar 64-bit add per plane and link: the cheaper form when scalar
-// registers are free); otherwise it is added to the per-lane 32-bit index.
-template <bool UB, typename T>
-__device__ __forceinline__ T ld_col(const T* plane, int uni, uint32_t lane) {
-    if constexpr (UB) return ld_plane(plane + uni, lane);
-    else return ld_plane(plane, lane + (uint32_t)uni);
-}
+// x3 (uniform); K = x3 parity relative to the column's first link selects the
+// x0 offsets.
 
-template <typename T, int MU, int K, bool UB>
-__device__ __forceinline__ void staples(const LatDev& L, const T* chain, uint64_t curw, int p, uint32_t pos,
-                                        const ColNbr& nb, int x3, T& C, T& S) {
-    using M = Math<T>;
+// A point in program order that v passes through: empty, but instructions that
+// make v stay before it and those that use v after it.  Between the links of a
+// thread it keeps the compiler from running several links' arithmetic side by
+// side, whose live values would cost wavefronts (FP64: 256 registers).
+template <typename T>
+__device__ __forceinline__ void pin(T& v) {
+    asm volatile("" : "+v"(v));
+}
+__device__ __forceinline__ void pin_uniform(int& v) { asm volatile("" : "+s"(v)); }
+
+// A link's angles: per direction NU the six of its two plaquettes, and its own.
+template <typename T>
+struct LinkLoads {
+    T v[3][6];
+    T own;
+};
+
+// Issue the 19 loads of link (MU, x).
+template <typename T, int MU, int K>
+__device__ __forceinline__ void load_link(const LatDev& L, const ChainBuf<T>& cb, uint64_t curw, int p, const ColNbr& nb,
+                                          int x3, LinkLoads<T>& q) {
+    constexpr int E = (int)sizeof(T);
     const int vu[4] = {nb.up0[K], nb.up1, nb.up2, 0};
     const int vd[4] = {nb.dn0[K], nb.dn1, nb.dn2, 0};
-    const int sh = (int)L.P * x3;   // the link's own x3, uniform
-    const int su[4] = {sh, sh, sh, sh + (x3 == L.L - 1 ? -L.hwrap[3] : L.hstr[3])};
-    const int sd[4] = {0, 0, 0, x3 == 0 ? L.hwrap[3] : -L.hstr[3]};
-    const int q = p ^ 1;
-    const T* pmu_q = plane_ptr(chain, curw, 2 * MU + q, L.V2);
+    const int sh = (int)L.P * x3 * E;   // the link's own x3, uniform
+    const int su[4] = {sh, sh, sh, sh + (x3 == L.L - 1 ? -L.hwrap[3] : L.hstr[3]) * E};
+    const int sd[4] = {0, 0, 0, (x3 == 0 ? L.hwrap[3] : -L.hstr[3]) * E};
+    const int o = p ^ 1;
+    const uint32_t mu_q = plane_off<T>(curw, 2 * MU + o, L.V2);
 #pragma unroll
     for (int NU = 0; NU < 4; ++NU) {
         if (NU == MU) continue;
-        const T* pnu_p = plane_ptr(chain, curw, 2 * NU + p, L.V2);
-        const T* pnu_q = plane_ptr(chain, curw, 2 * NU + q, L.V2);
-        const T t_nu_pmu = ld_col<UB>(pnu_q, su[MU], pos + vu[MU]);
-        const T t_mu_pnu = ld_col<UB>(pmu_q, su[NU], pos + vu[NU]);
-        const T t_nu_x = ld_col<UB>(pnu_p, sh, pos);
-        const T t_nu_pmu_mnu = ld_col<UB>(pnu_p, su[MU] + sd[NU], pos + (vu[MU] + vd[NU]));
-        const T t_mu_mnu = ld_col<UB>(pmu_q, sh + sd[NU], pos + vd[NU]);
-        const T t_nu_mnu = ld_col<UB>(pnu_q, sh + sd[NU], pos + vd[NU]);
-        const T sf = t_nu_pmu - t_mu_pnu - t_nu_x;
-        const T sb = t_nu_mnu - t_nu_pmu_mnu - t_mu_mnu;
+        const int j = NU - (NU > MU ? 1 : 0);
+        const uint32_t nu_p = plane_off<T>(curw, 2 * NU + p, L.V2);
+        const uint32_t nu_q = plane_off<T>(curw, 2 * NU + o, L.V2);
+        q.v[j][0] = cb.load(nb.pos + vu[MU], nu_q + su[MU]);                        // th_nu(x+mu)
+        q.v[j][1] = cb.load(nb.pos + vu[NU], mu_q + su[NU]);                        // th_mu(x+nu)
+        q.v[j][2] = cb.load(nb.pos, nu_p + sh);                                     // th_nu(x)
+        q.v[j][3] = cb.load(nb.pos + (vu[MU] + vd[NU]), nu_p + su[MU] + sd[NU]);    // th_nu(x+mu-nu)
+        q.v[j][4] = cb.load(nb.pos + vd[NU], mu_q + sh + sd[NU]);                   // th_mu(x-nu)
+        q.v[j][5] = cb.load(nb.pos + vd[NU], nu_q + sh + sd[NU]);                   // th_nu(x-nu)
+    }
+    q.own = cb.load(nb.pos, plane_off<T>(curw, 2 * MU + p, L.V2) + sh);
+}
+
+template <typename T>
+__device__ __forceinline__ void staple_sums(const LinkLoads<T>& q, T& C, T& S) {
+    using M = Math<T>;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {   // the directions other than mu, ascending
+        const T sf = q.v[j][0] - q.v[j][1] - q.v[j][2];
+        const T sb = q.v[j][5] - q.v[j][3] - q.v[j][4];
         T s1, c1, s2, c2;
         M::sincos_rad(sf, &s1, &c1);
         M::sincos_rad(sb, &s2, &c2);
-        if (NU == (MU == 0 ? 1 : 0)) {   // the first direction seeds the sums
+        if (j == 0) {   // the first direction seeds the sums
             C = c1 + c2;
             S = s1 + s2;
         } else {
@@ -202,33 +256,41 @@ __device__ __forceinline__ void staples(const LatDev& L, const T* chain, uint64_
     }
 }
 
-// Staples and old angle of the LPT links of the thread's column; hl, in: the
-// links' half indices and whether they lie in the lattice (pos < P, and
-// x3 < L, uniform over the wavefront).
-template <typename T, int MU, int LPT, bool UB>
-__device__ __forceinline__ void col_staples(const LatDev& L, const T* chain, uint64_t curw, int p, const ColTile& ct,
-                                            const ColNbr& nb, uint32_t pos, const T* pown, T* C, T* S, T* t_old,
-                                            uint32_t* hl, bool* in) {
+// Staples and old angle of the LPT links of the thread's column.  The 19 loads
+// of a link are issued together, AHEAD links before their sums: left alone, the
+// scheduler saves registers by spreading them among the sums, one or two in
+// flight at a time (heatbath of L = 20 x 128, FP32: 133 us so, 92 with a link's
+// loads together, 88 with the next link's ahead).  Overrelaxation of L = 12 x 64
+// FP32: 8.7 -> 7.4 us; of L = 20 x 128 67 -> 64, 5.7 TB/s.  Links past the lattice's end (x3 >= L, uniform) load the
+// last one's and are not used.
+template <typename T, int MU, int LPT, int AHEAD>
+__device__ __forceinline__ void col_staples(const LatDev& L, const ChainBuf<T>& cb, uint64_t curw, int p,
+                                            const ColTile& ct, const ColNbr& nb, T* C, T* S, T* t_old) {
+    LinkLoads<T> q[AHEAD + 1];
+    auto load = [&](int r) __attribute__((always_inline)) {
+        int x3 = min(ct.x3_0 + r, L.L - 1);
+        pin_uniform(x3);
+        if (r & 1) load_link<T, MU, 1>(L, cb, curw, p, nb, x3, q[r % (AHEAD + 1)]);
+        else load_link<T, MU, 0>(L, cb, curw, p, nb, x3, q[r % (AHEAD + 1)]);
+    };
+#pragma unroll
+    for (int r = 0; r < AHEAD && r < LPT; ++r) load(r);
 #pragma unroll
     for (int r = 0; r < LPT; ++r) {
-        const int x3 = ct.x3_0 + r;
-        C[r] = T(0); S[r] = T(0); t_old[r] = T(0);
-        hl[r] = pos + L.P * (uint32_t)x3;
-        in[r] = ct.in_slab && x3 < L.L;
-        if (x3 < L.L) {
-            if (r & 1) staples<T, MU, 1, UB>(L, chain, curw, p, pos, nb, x3, C[r], S[r]);
-            else staples<T, MU, 0, UB>(L, chain, curw, p, pos, nb, x3, C[r], S[r]);
-            t_old[r] = ld_col<UB>(pown, (int)L.P * x3, pos);
-        }
+        if (r + AHEAD < LPT) load(r + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+        staple_sums(q[r % (AHEAD + 1)], C[r], S[r]);
+        t_old[r] = q[r % (AHEAD + 1)].own;
+        pin(C[r]);
+        pin(S[r]);
+        pin(t_old[r]);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// Reduce the per-thread fixed-point values of a block; returns the block sum
-// in thread 0.
+// Sum of the wavefronts' values of a block, in thread 0.
 __device__ __forceinline__ long long block_sum_i64(long long v) {
     __shared__ long long part[kBlock / 64];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) part[wid] = v;
     __syncthreads();
@@ -279,7 +341,6 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
     // constants (the same operations, so the same values), which keeps the
     // block's LDS small enough for one more resident block per CU
     __shared__ T s_ak[NT], s_ch[NT], s_sh[NT];
-    __shared__ unsigned char s_res[NT];
     __shared__ short s_queue[2][NT];
     __shared__ int s_qn[2];
     int li = 0;
@@ -288,8 +349,8 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
     const LatDev& L = lt.l[li];
     if (mode == kModeApproach && s.lat_done[li]) return;
     const int rel = b - L.hb_block0;
-    const int cl = rel / L.hb_bpc;
-    const int tile = rel - cl * L.hb_bpc;
+    int tile;
+    const int cl = udiv(rel, L.hb_bpc, L.m_hb, tile);
     const int g = L.chain0 + cl;
     const int colour = 2 * MU + parity;
     const int tid = threadIdx.x;
@@ -300,129 +361,145 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
     const uint32_t sweep = kind == kApproach ? *s.approach_ctr : *s.sweep_ctr;
     const uint32_t c1base = ctr1_word(0, (uint32_t)colour, (uint32_t)kind, (uint32_t)L.lat_id);
     const uint32_t c3 = (uint32_t)(gi - L.itv0);
-    const int own = (int)((curw >> (8 * colour)) & 1ull);
-    T* pcur = chain + (size_t)(own * 8 + colour) * L.V2;
-    const T* pown = pcur;
+    const ChainBuf<T> cb(chain, L.V2);
+    const uint32_t o_cur = plane_off<T>(curw, colour, L.V2);
+    const uint32_t o_alt = plane_off<T>(curw, colour, L.V2, 1);
     // the fused pass's in-place store; a tuner's timing launch leaves the
     // state as it is and writes both angles into the non-current plane
-    T* pinpl = mode == kModeTune ? chain + (size_t)((own ^ 1) * 8 + colour) * L.V2 : pcur;
-    T* palt = chain + (size_t)((own ^ 1) * 8 + colour) * L.V2;
+    const uint32_t o_inpl = mode == kModeTune ? o_alt : o_cur;
     const ColTile ct = col_tile<LPT>(L, tile, tid);
-    const ColNbr nb = col_nbr(L, ct, parity);
+    const ColNbr nb = col_nbr(L, ct, parity, (int)sizeof(T));
     const uint32_t pos = ct.pos;
 
-    T C[LPT], S[LPT], t_old[LPT];
-    uint32_t hl[LPT];
-    bool in[LPT];
-    col_staples<T, MU, LPT, false>(L, chain, curw, parity, ct, nb, pos, pown, C, S, t_old, hl, in);
-    if (tid == 0) s_qn[0] = 0;
-    T eps_old[LPT], R[LPT], kap[LPT], ch[LPT], sh[LPT];
+    // Straight-line code per link: lanes past the slab compute position 0's
+    // links and are masked where it matters (queue, stores, sums), and cases that
+    // almost never occur branch on the whole wavefront.  Divergent branches here
+    // cost a register copy per live value at every merge.
+    T C[LPT], S[LPT], t_old[LPT], eps_old[LPT], R[LPT], ch[LPT], sh[LPT];
     T t_or_old[LPT];   // fused pass: the old angle's overrelaxation, from the sine and cosine at hand
-    bool got[LPT];
+    if (tid == 0) s_qn[0] = 0;
+    col_staples<T, MU, LPT, kHbAhead>(L, cb, curw, parity, ct, nb, C, S, t_old);
 #pragma unroll
     for (int r = 0; r < LPT; ++r) {
-        const uint32_t h = hl[r];
-        const int e = r * kBlock + tid;
-        got[r] = true;
-        ch[r] = T(1); sh[r] = T(0); eps_old[r] = T(0); R[r] = T(0); kap[r] = T(0);
-        t_or_old[r] = T(0);
-        if (in[r]) {
-            T so, co;
-            M::sincos_rad(t_old[r], &so, &co);
-            eps_old[r] = fms2(C[r], co, S[r], so);
-            if constexpr (VAR == kHbFuseOr) t_or_old[r] = or_angle_sc(t_old[r], so, co, C[r], S[r]);
-            R[r] = M::sqrt_(fma2(C[r], C[r], S[r], S[r]));
-            kap[r] = (T)acoup * R[r];
-            const T ak = kap[r] < T(0) ? -kap[r] : kap[r];
-            T q, rm1, kg2;
-            vm_constants(ak, q, rm1, kg2);
-            const uint4 w = philox10(make_uint4(h, c1base, sweep, c3), k0, k1);
-            if (ak == T(0)) {
-                M::sincos_halfpi_w(w.x, &sh[r], &ch[r]);
-            } else {
-                got[r] = vm_attempt(w.x, w.y, q, rm1, kg2, ch[r], sh[r]);
-                if (!got[r]) got[r] = vm_attempt(w.z, w.w, q, rm1, kg2, ch[r], sh[r]);
-            }
-            if (!got[r]) {
-                s_ak[e] = ak;
-                s_res[e] = 0;
-            }
-        }
+        T so, co;
+        pin(C[r]);
+        pin(S[r]);
+        pin(t_old[r]);
+        M::sincos_rad(t_old[r], &so, &co);
+        eps_old[r] = fms2(C[r], co, S[r], so);
+        if constexpr (VAR == kHbFuseOr) t_or_old[r] = or_angle_sc(t_old[r], so, co, C[r], S[r]);
+        R[r] = M::sqrt_(fma2(C[r], C[r], S[r], S[r]));
+        const T ak = M::abs_((T)acoup * R[r]);
+        T q, rm1, kg2;
+        vm_constants(ak, q, rm1, kg2);
+        const uint4 w = philox10(make_uint4(pos + L.P * (uint32_t)(ct.x3_0 + r), c1base, sweep, c3), k0, k1);
+        const bool ok = vm_first_two(w, ak, q, rm1, kg2, ch[r], sh[r]);
+        ch[r] = ok ? ch[r] : T(2);   // no cosine: not accepted yet
+        if constexpr (VAR == kHbFuseOr) pin(t_or_old[r]);
+        pin(eps_old[r]);
+        pin(R[r]);
+        pin(ch[r]);
+        pin(sh[r]);
+        __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < LPT; ++r)
-        if (!got[r]) s_queue[0][atomicAdd(&s_qn[0], 1)] = (short)(r * kBlock + tid);
+        if (ch[r] == T(2) && ct.in_slab && ct.x3_0 + r < L.L) {   // a link of the lattice
+            const int e = r * kBlock + tid;
+            s_queue[0][atomicAdd(&s_qn[0], 1)] = (short)e;
+            s_ak[e] = M::abs_((T)acoup * R[r]);
+            s_ch[e] = T(2);
+        }
     __syncthreads();
     int cq = 0;
-    for (int m = 1; m < kVmCap / 2; ++m) {
+    // rounds after the first find a handful of links (0.7 % of the class): they
+    // are dealt 2^lg lanes each, one attempt pair per lane, the first success in
+    // attempt order wins, and the block is done
+    for (int m = 1; m < kVmCap / 2;) {
         const int n = s_qn[cq];
         if (n == 0) break;
         if (tid == 0) s_qn[cq ^ 1] = 0;
         __syncthreads();
-        for (int i = tid; i < n; i += kBlock) {
+        int lg = 0;
+        if (m > 1)
+            while (lg < 4 && (n << (lg + 1)) <= 64 && m + (1 << (lg + 1)) <= kVmCap / 2) ++lg;
+        const int sub = tid & ((1 << lg) - 1);
+        for (int i = tid >> lg; i < n; i += kBlock >> lg) {
             const int e = s_queue[cq][i];
             // queue entry e = r kBlock + tid: link r of thread tid
             const uint32_t he = ct.pos0 + (uint32_t)(e & (kBlock - 1)) + L.P * (uint32_t)(ct.x3_0 + e / kBlock);
-            const uint4 w = philox10(make_uint4(he, c1base | (uint32_t)m, sweep, c3), k0, k1);
+            const uint4 w = philox10(make_uint4(he, c1base | (uint32_t)(m + sub), sweep, c3), k0, k1);
             T qe, rme, kge;
             vm_constants(s_ak[e], qe, rme, kge);
             T che = T(1), she = T(0);
-            bool acc = vm_attempt(w.x, w.y, qe, rme, kge, che, she);
-            if (!acc) acc = vm_attempt(w.z, w.w, qe, rme, kge, che, she);
-            if (acc) {
+            const bool a0 = vm_attempt(w.x, w.y, qe, rme, kge, che, she);
+            T c1, s1;
+            const bool a1 = vm_try(w.z, w.w, qe, rme, kge, c1, s1);
+            che = a0 ? che : c1;
+            she = a0 ? she : s1;
+            const unsigned long long ok = __ballot(a0 | a1);
+            const int g0 = (tid & 63) & ~((1 << lg) - 1);   // the link's first lane
+            const unsigned gm = (unsigned)(ok >> g0) & ((1u << (1 << lg)) - 1u);
+            if (gm ? sub == __ffs((int)gm) - 1 : false) {
                 s_ch[e] = che;
                 s_sh[e] = she;
-                s_res[e] = 1;
-            } else {
-                s_queue[cq ^ 1][atomicAdd(&s_qn[cq ^ 1], 1)] = (short)e;
             }
+            if (!gm && sub == 0) s_queue[cq ^ 1][atomicAdd(&s_qn[cq ^ 1], 1)] = (short)e;
         }
         __syncthreads();
+        m += 1 << lg;
         cq ^= 1;
     }
     long long fx = 0;
     int fx32 = 0;   // FP32: the thread's class links at 2^-25 (|dE| <= 12 per link, LPT <= 4)
+    if (ct.in_slab) {
 #pragma unroll
-    for (int r = 0; r < LPT; ++r) {
-        const uint32_t h = hl[r];
-        if (!in[r]) continue;
-        const int e = r * kBlock + tid;
-        bool ok = got[r];
-        T c_ = ch[r], s_ = sh[r];
-        if (!ok && s_res[e]) {
-            c_ = s_ch[e];
-            s_ = s_sh[e];
-            ok = true;
+        for (int r = 0; r < LPT; ++r) {
+            const int x3 = ct.x3_0 + r;
+            if (x3 >= L.L) continue;   // uniform
+            const int e = r * kBlock + tid;
+            if (ch[r] == T(2)) {
+                ch[r] = s_ch[e];
+                sh[r] = s_sh[e];
+            }
+            // a link at the attempt cap keeps its angle
+            const bool lost = ch[r] == T(2);
+            const uint32_t uni = L.P * (uint32_t)x3 * (uint32_t)sizeof(T);
+            const T kap = (T)acoup * R[r];
+            T dE, t_new, t_or_new;
+            if constexpr (VAR == kHbFuseOr) hb_or_new_angle(ch[r], sh[r], C[r], S[r], R[r], kap, eps_old[r], t_or_new, dE);
+            else hb_new_angle(ch[r], sh[r], C[r], S[r], R[r], kap, eps_old[r], t_new, dE);
+            if (any_lane(lost)) {
+                dE = lost ? T(0) : dE;
+                if constexpr (VAR == kHbFuseOr) t_or_new = lost ? t_or_old[r] : t_or_new;
+                else t_new = lost ? cb.load(nb.pos, o_cur + uni) : t_new;
+            }
+            if constexpr (VAR == kHbFuseOr) {
+                // the class's overrelaxation follows at once, on the same staples:
+                // of the heatbath candidate into the alternate plane, of the old
+                // angle in place; the pass's decision picks the plane
+                cb.store(nb.pos, o_alt + uni, t_or_new);
+                cb.store(nb.pos, o_inpl + uni, t_or_old[r]);
+            } else {
+                cb.store(nb.pos, o_alt + uni, t_new);
+            }
+            if constexpr (VAR == kHbPre) {
+                const size_t j = (size_t)L.lbase + (size_t)cl * L.V2 + L.P * (uint32_t)x3 + pos;
+                T* lc = static_cast<T*>(s.link_cst);
+                s.link_d[j] = lost ? kLinkNone : link_fixed(dE, L);
+                lc[j] = C[r];
+                lc[s.link_n + j] = S[r];
+                lc[2 * s.link_n + j] = cb.load(nb.pos, o_cur + uni);
+            }
+            if constexpr (M::f32) fx32 += __float2int_rn(dE * 33554432.0f);
+            else fx += to_fixed((double)dE, L);
         }
-        T t_new = t_old[r];
-        T dE = T(0);
-        if constexpr (VAR == kHbFuseOr) {
-            // the class's overrelaxation follows at once, on the same staples:
-            // of the heatbath candidate into the alternate plane, of the old
-            // angle in place; the pass's decision picks the plane
-            T t_or_new = t_or_old[r];
-            if (ok) hb_or_new_angle(c_, s_, C[r], S[r], R[r], kap[r], eps_old[r], t_or_new, dE);
-            st_plane(palt, h, t_or_new);
-            st_plane(pinpl, h, t_or_old[r]);
-        } else {
-            if (ok) hb_new_angle(c_, s_, C[r], S[r], R[r], kap[r], eps_old[r], t_new, dE);
-            st_plane(palt, h, t_new);
-        }
-        if constexpr (VAR == kHbPre) {
-            const size_t j = (size_t)L.lbase + (size_t)cl * L.V2 + h;
-            T* lc = static_cast<T*>(s.link_cst);
-            s.link_d[j] = ok ? link_fixed(dE, L) : kLinkNone;
-            lc[j] = C[r];
-            lc[s.link_n + j] = S[r];
-            lc[2 * s.link_n + j] = t_old[r];
-        }
-        if constexpr (M::f32) fx32 += __float2int_rn(dE * 33554432.0f);
-        else fx += to_fixed((double)dE, L);
     }
     if constexpr (VAR == kHbPre) return;
-    if constexpr (M::f32) fx = (long long)fx32 << (L.fxb - 25);
-    const long long tot = block_sum_i64(fx);
+    long long tot;
+    if constexpr (M::f32) tot = block_sum_i64(wave_sum_i32(fx32)) << (L.fxb - 25);
+    else tot = block_sum_i64(wave_sum_i64(fx));
     long long total = 0;
     if (threadIdx.x == 0 && chain_arrive(s.acc + g, tot, L.hb_bpc, &total)) {
         const double E0 = s.E[g];
@@ -470,12 +547,17 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
     }
 }
 
-// The plain FP32 pass with 4 class links per thread: registers kept to 72
-// so that seven wavefronts per SIMD fit (the LDS of the queue allows more).
-// Measured: heatbath 98.1 -> 97.0 us at L=20 x 128; the fused pass, capped
-// the same way, slowed from 108 to 132 us, so it keeps its registers.
+// With 4 class links per thread the registers are kept to 72 (FP32, seven
+// wavefronts per SIMD) and 128 (FP64, four), which they fit without spills.
+// The FP32 pass is bound by vector-instruction issue: 314 per class link (332
+// before the straight-line links and the buffer addressing), of which about 45
+// are a wavefront's prologue, queue and reduction shared by its 4 links.
+// Heatbath of L = 20 x 128 FP32: 97.2 -> 88.4 us (six wavefronts 92, eight 89.6,
+// a link's loads without the next link's ahead of it 91.9); L = 12 x 64 FP32, 2
+// links: 16.1 -> 13.9 us; L = 12 x 64 FP64: 41.7 -> 39.4; the fused pass of
+// L = 14 x 74: 26.7 -> 23.5.
 template <typename T, int LPT, int VAR>
-struct HbWaves { static constexpr int value = (sizeof(T) == 4 && LPT == 4 && VAR == kHbPlain) ? 7 : 1; };
+struct HbWaves { static constexpr int value = LPT == 4 ? (sizeof(T) == 4 ? 7 : 4) : 1; };
 
 template <typename T, int MU, int LPT, int VAR>
 __global__ __launch_bounds__(kBlock, (HbWaves<T, LPT, VAR>::value)) void k_hb(LatTable lt, T* __restrict__ th, DevState s, int parity, int mode,
@@ -787,26 +869,25 @@ __device__ __forceinline__ void or_block(const LatTable& lt, T* __restrict__ th,
     while (li + 1 < lt.n && b >= lt.l[li + 1].or_block0) ++li;
     const LatDev& L = lt.l[li];
     const int rel = b - L.or_block0;
-    const int cl = rel / L.or_bpc;
-    const int tile = rel - cl * L.or_bpc;
+    int tile;
+    const int cl = udiv(rel, L.or_bpc, L.m_or, tile);
     const int g = L.chain0 + cl;
     const int colour = 2 * MU + parity;
     const uint64_t curw = *reinterpret_cast<const uint64_t*>(s.cur + 8 * g);
     T* chain = chain_base(L, th, cl);
-    T* pown = plane_ptr(chain, curw, colour, L.V2);
+    const ChainBuf<T> cb(chain, L.V2);
     // timing runs of the tuner write to the non-current plane (state unchanged)
-    T* pout = to_alt ? chain + (size_t)(((((curw >> (8 * colour)) & 1ull) ^ 1ull) * 8ull) + colour) * L.V2 : pown;
+    const uint32_t o_out = plane_off<T>(curw, colour, L.V2, to_alt ? 1 : 0);
     const ColTile ct = col_tile<LPT>(L, tile, (int)threadIdx.x);
-    const ColNbr nb = col_nbr(L, ct, parity);
-    const uint32_t pos = ct.pos;
+    const ColNbr nb = col_nbr(L, ct, parity, (int)sizeof(T));
     T C[LPT], S[LPT], t_old[LPT];
-    uint32_t hl[LPT];
-    bool in[LPT];
-    col_staples<T, MU, LPT, true>(L, chain, curw, parity, ct, nb, pos, pown, C, S, t_old, hl, in);
+    col_staples<T, MU, LPT, kOrAhead>(L, cb, curw, parity, ct, nb, C, S, t_old);
 #pragma unroll
     for (int r = 0; r < LPT; ++r) {
-        if (!in[r]) continue;
-        st_plane(pout, hl[r], or_angle(t_old[r], C[r], S[r]));
+        const int x3 = ct.x3_0 + r;
+        if (x3 >= L.L) continue;   // uniform
+        const T t_new = or_angle(t_old[r], C[r], S[r]);
+        if (ct.in_slab) cb.store(nb.pos, o_out + L.P * (uint32_t)x3 * (uint32_t)sizeof(T), t_new);
     }
 }
 
@@ -868,7 +949,7 @@ __global__ __launch_bounds__(kBlock) void k_energy(LatTable lt, const T* __restr
             }
     }
     if (__syncthreads_or(bad) && threadIdx.x == 0) atomicOr(s.health + g, (uint32_t)kHealthNonFinite);
-    const long long tot = block_sum_i64(fx);
+    const long long tot = block_sum_i64(wave_sum_i64(fx));
     long long total = 0;
     if (threadIdx.x == 0 && chain_arrive(s.eacc + g, tot, L.ebpc, &total)) {
         const double En = (double)total * L.fxinv;
@@ -894,7 +975,7 @@ __global__ __launch_bounds__(kBlock) void k_energy(LatTable lt, const T* __restr
     }
     if (OBS) {
         __syncthreads();   // block_sum_i64's shared partials are reused
-        const long long ta = block_sum_i64(fa);
+        const long long ta = block_sum_i64(wave_sum_i64(fa));
         long long tb = 0;
         if (threadIdx.x == 0 && chain_arrive(s.oacc + g, ta, L.ebpc, &tb)) {
             s.obs[g] = (double)tb * L.fxinv;
