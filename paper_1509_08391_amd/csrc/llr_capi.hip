@@ -96,6 +96,7 @@ struct llr_ctx {
     DevState ds{};
     bool laid_out = false;
     bool resident = false;     // every lattice's chain fits in LDS (chain-resident sweeps)
+    bool resident_link = false;   // with a class's candidates of the per-link restriction too
     void* state = nullptr;
     size_t state_bytes = 0;
     bool have_energy = false;
@@ -320,7 +321,8 @@ static llr_status layout(llr_ctx* c) {
     for (int i = 0; i < n; ++i) ident[i] = i;
     HIPCHK(hipMemcpyAsync(s.itv, ident.data(), n * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(s.conf, ident.data(), n * 4, hipMemcpyHostToDevice, c->stream));
-    c->resident = chain_fits(lt, elem_size(c));
+    c->resident = chain_fits(lt, elem_size(c), false);
+    c->resident_link = chain_fits(lt, elem_size(c), true);
     if (c->resident) HIPCHK(chain_setup());
     c->approach_sweeps.assign(lt.n, 0);
     c->laid_out = true;
@@ -426,11 +428,11 @@ static bool plain_mode(int mode) {
     return mode == LLR_MODE_RESTRICTED || mode == LLR_MODE_FREE || mode == LLR_MODE_MUCA;
 }
 
-// Whether sweeps of this mode run chain-resident: every chain fits in LDS, the
-// links of a class are drawn independently, and no per-kernel timing is asked
-// for (its figures are those of the class-pass kernels).
+// Whether sweeps of this mode run chain-resident: every chain fits in LDS and no
+// per-kernel timing is asked for (its figures are those of the class-pass
+// kernels).
 static bool resident_sweeps(const llr_ctx* c, int mode) {
-    return c->resident && !c->timing && (plain_mode(mode) || mode == LLR_MODE_APPROACH);
+    return (mode == LLR_MODE_LINK ? c->resident_link : c->resident) && !c->timing;
 }
 
 static int recompute_check(int mode) {

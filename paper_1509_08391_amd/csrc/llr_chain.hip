@@ -18,6 +18,7 @@
 
 #include "llr_internal.hpp"
 #include "llr_link.hpp"
+#include "llr_walk.hpp"
 
 namespace llr {
 
@@ -196,11 +197,16 @@ __device__ __forceinline__ void chain_tail(bool (&got)[LPT], T (&ch)[LPT], T (&s
 // Decisions, counters, measurement and recompute are those of the last block
 // of a class pass, k_end_sweep and k_energy; every thread takes the class
 // decision itself from the block's partial sums, which saves a barrier.
-// FUSED: the interleaved order, each heatbath followed by its class's
-// overrelaxation on the same staples.
-template <typename T, int LPT, int MAXT, bool FUSED>
+// VAR kHbFuseOr: the interleaved order, each heatbath followed by its class's
+// overrelaxation on the same staples.  kHbPre: the restriction per link; the
+// class's candidates go to LDS (behind the planes) and, in place, to its plane,
+// and the first wavefront walks them.  A launch of one pass waits for the chain
+// with most re-draws (L = 8 x 32 FP32: 60 us a pass, the chains' mean 15); here
+// each chain goes on to its next pass by itself (534 -> 203 us per sweep).
+template <typename T, int LPT, int MAXT, int VAR>
 __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ th, DevState s, ChainArgs a) {
     using M = Math<T>;
+    constexpr bool FUSED = VAR == kHbFuseOr;
     extern __shared__ __align__(16) char lat[];   // 8 planes of V/2 angles
     __shared__ long long part[2][MAXT / 64];
     __shared__ int w_h[MAXT / 64][64];
@@ -235,7 +241,7 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
         const bool b_half = a.order == 2 && cl >= (L.n_chains + 1) / 2;   // staggered: overrelaxation first
         double E = s.E[g];
         double sumE = a.measure_from < a.n_sweeps ? s.sumE[gi] : 0.0;
-        unsigned prop = 0, nacc = 0, nfused = 0, bits = 0;
+        unsigned prop = 0, nacc = 0, nfused = 0, bits = 0, fixes = 0, arcs = 0;
         int flip = 0;   // which half of `part` the next reduction uses
         __syncthreads();
 #pragma unroll 1
@@ -288,6 +294,39 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                     }
                 }
                 chain_tail<T, LPT>(got, ch, sh, ak, k, w_h[wid], w_ak[wid], c1base, sweep, c3, a.k0, a.k1);
+                if constexpr (VAR == kHbPre) {
+                    long long* sd = reinterpret_cast<long long*>(lat + 8 * pb);
+                    T* sc = reinterpret_cast<T*>(sd + V2);
+                    T *ss = sc + V2, *st = ss + V2;
+#pragma unroll
+                    for (int r = 0; r < LPT; ++r) {
+                        T tn = t_old[r], dE = T(0);
+                        if (got[r]) hb_new_angle(ch[r], sh[r], C[r], S[r], R[r], kap[r], eps_old[r], tn, dE);
+                        const int h = r * NT + tid;
+                        if (h < V2) {
+                            sd[h] = got[r] ? link_fixed(dE, L) : kLinkNone;
+                            sc[h] = C[r];
+                            ss[h] = S[r];
+                            st[h] = t_old[r];
+                            *reinterpret_cast<T*>(own + k[r].hb) = tn;
+                        }
+                    }
+                    __syncthreads();
+                    if (wid == 0) {
+                        Walk w = walk_begin(L, colour, (int)kind, sweep, c3, a.k0, a.k1, afix, E, lo, hi);
+                        walk_links<T>(L, w, 0u, V2, sd, sc, ss, st,
+                                      [&](uint32_t h, T v) { *reinterpret_cast<T*>(own + h * (uint32_t)sizeof(T)) = v; });
+                        if (lane == 0) part[0][0] = w.Ssum;
+                        fixes += w.fixes;
+                        arcs += w.arcs;
+                    }
+                    __syncthreads();
+                    E += (double)part[0][0] * (L.fxinv / (double)(1 << kWalkBits));
+                    prop += 1;
+                    nacc += 1;
+                    bits |= 1u << colour;
+                    continue;   // the next write of part[0][0] follows two more barriers
+                }
                 T t_new[LPT];
                 long long fx = 0;
                 int fx32 = 0;
@@ -420,6 +459,10 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
             s.hb_prop[g] += prop;
             s.hb_acc[g] += nacc;
             s.fu_acc[g] += nfused;
+            if constexpr (VAR == kHbPre) {
+                s.link_fix[g] += fixes;
+                s.link_arc[g] += arcs;
+            }
         }
     }
     if (idle && a.end_sweep && tid == 0) {
@@ -448,20 +491,27 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
 // chains 140.5 / 121.3, 512 chains 141.1 / 123.2.
 constexpr size_t kChainLds = 131072;
 
-bool chain_fits(const LatTable& lt, size_t elem) {
+static size_t chain_lds(uint32_t v2, size_t elem, bool per_link) {
+    return v2 * (8 * elem + (per_link ? 8 + 3 * elem : 0));
+}
+
+// Whether every lattice's chain fits; per_link: with the candidates of a class
+// (L = 8 in FP32, L = 6 in FP64)
+bool chain_fits(const LatTable& lt, size_t elem, bool per_link) {
     for (int i = 0; i < lt.n; ++i)
-        if (8 * (size_t)lt.l[i].V2 * elem > kChainLds) return false;
+        if (chain_lds(lt.l[i].V2, elem, per_link) > kChainLds) return false;
     return lt.n > 0;
 }
 
+template <typename T, int LPT, int MAXT, int VAR>
+static hipError_t allow_lds() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chain<T, LPT, MAXT, VAR>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainLds);
+}
 template <typename T, int LPT, int MAXT>
 static hipError_t shape_setup() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chain<T, LPT, MAXT, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainLds);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chain<T, LPT, MAXT, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainLds);
-    return e;
+    const hipError_t e = allow_lds<T, LPT, MAXT, kHbPlain>();
+    return e == hipSuccess ? allow_lds<T, LPT, MAXT, kHbFuseOr>() : e;
 }
 
 // the current device's kernels may use more than the default 64 KB of LDS
@@ -471,21 +521,32 @@ hipError_t chain_setup() {
     if (e == hipSuccess) e = shape_setup<float, 4, 512>();
     if (e == hipSuccess) e = shape_setup<double, 1, 1024>();
     if (e == hipSuccess) e = shape_setup<double, 2, 1024>();
+    if (e == hipSuccess) e = allow_lds<float, 1, 1024, kHbPre>();
+    if (e == hipSuccess) e = allow_lds<float, 2, 1024, kHbPre>();
+    if (e == hipSuccess) e = allow_lds<double, 1, 1024, kHbPre>();
     return e;
 }
 
+template <typename T, int LPT, int MAXT, int VAR>
+static void launch_var(const LatTable& lt, T* th, DevState s, const ChainArgs& a, uint32_t v2, hipStream_t st) {
+    const dim3 gr(lt.n_chains), bl(((v2 + LPT - 1) / LPT + 63) / 64 * 64);
+    hipLaunchKernelGGL((k_chain<T, LPT, MAXT, VAR>), gr, bl, chain_lds(v2, sizeof(T), VAR == kHbPre), st, lt, th, s, a);
+}
 template <typename T, int LPT, int MAXT>
 static void launch_shape(const LatTable& lt, T* th, DevState s, const ChainArgs& a, uint32_t v2, hipStream_t st) {
-    const dim3 gr(lt.n_chains), bl(((v2 + LPT - 1) / LPT + 63) / 64 * 64);
-    const size_t lds = 8 * (size_t)v2 * sizeof(T);
-    if (a.order == 1) hipLaunchKernelGGL((k_chain<T, LPT, MAXT, true>), gr, bl, lds, st, lt, th, s, a);
-    else hipLaunchKernelGGL((k_chain<T, LPT, MAXT, false>), gr, bl, lds, st, lt, th, s, a);
+    if (a.order == 1) launch_var<T, LPT, MAXT, kHbFuseOr>(lt, th, s, a, v2, st);
+    else launch_var<T, LPT, MAXT, kHbPlain>(lt, th, s, a, v2, st);
 }
 
 template <typename T>
 void launch_chain(const LatTable& lt, T* th, DevState s, const ChainArgs& a, hipStream_t st) {
     uint32_t v2 = 0;
     for (int i = 0; i < lt.n; ++i) v2 = v2 > lt.l[i].V2 ? v2 : lt.l[i].V2;
+    if (a.mode == kModeLink) {
+        if (v2 <= 1024) launch_var<T, 1, 1024, kHbPre>(lt, th, s, a, v2, st);
+        else if constexpr (sizeof(T) == 4) launch_var<T, 2, 1024, kHbPre>(lt, th, s, a, v2, st);
+        return;
+    }
     if (v2 <= 1024) {
         launch_shape<T, 1, 1024>(lt, th, s, a, v2, st);
         return;

@@ -131,7 +131,7 @@ struct ChainArgs {
 
 // chain-resident sweeps (llr_chain.hip): whether every lattice's chain fits in
 // LDS, and the launch (one block per chain)
-bool chain_fits(const LatTable& lt, size_t elem);
+bool chain_fits(const LatTable& lt, size_t elem, bool per_link);
 hipError_t chain_setup();
 template <typename T> void launch_chain(const LatTable& lt, T* th, DevState s, const ChainArgs& a, hipStream_t st);
 

@@ -15,6 +15,9 @@ namespace llr {
 // accepted, no counters touched; the walk kernel then decides)
 enum { kModeRestricted = 0, kModeApproach = 1, kModeFree = 2, kModeMuca = 3, kModeLink = 4,
        kModeTune = kHbModeTune, kModeLinkPre = 6 };
+// instantiations of a heatbath pass: plain, with the restriction per link (the
+// class pass then only writes candidates), followed by the class's overrelaxation
+enum { kHbPlain = 0, kHbPre = 1, kHbFuseOr = 2 };
 // Whether a condition that almost never holds does so on any lane: one compare
 // and a scalar branch, where a select would cost every lane an instruction per
 // value and a divergent branch the copies of its merge.
@@ -108,17 +111,24 @@ __device__ __forceinline__ long long dpp_add(long long v) {
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, ROWS, 0xf, false);
     return v + (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
-__device__ __forceinline__ long long wave_sum_i64(long long v) {
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its sum
+// inclusive prefix sums within each row of 16 lanes (row_shr:1, 2, 4, 8)
+__device__ __forceinline__ long long row_scan_i64(long long v) {
+    v = dpp_add<0x111, 0xf>(v);
     v = dpp_add<0x112, 0xf>(v);
     v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the sum
-    const int lo = __builtin_amdgcn_readlane((int)v, 63);
-    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), 63);
-    return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+    return dpp_add<0x118, 0xf>(v);
 }
+// over the wavefront
+__device__ __forceinline__ long long wave_scan_i64(long long v) {
+    v = row_scan_i64(v);
+    v = dpp_add<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v); // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ long long lane_i64(long long v, int lane) {
+    return (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) |
+                       (unsigned)__builtin_amdgcn_readlane((int)v, lane));
+}
+__device__ __forceinline__ long long wave_sum_i64(long long v) { return lane_i64(wave_scan_i64(v), 63); }
 
 // The same for 32-bit values: their 16-bit halves add up without overflow, and
 // each step is one instruction with a DPP operand.

@@ -17,16 +17,13 @@
 
 #include "llr_internal.hpp"
 #include "llr_link.hpp"
+#include "llr_walk.hpp"
 
 namespace llr {
 
-// instantiations of the heatbath class pass
-enum { kHbPlain = 0, kHbPre = 1, kHbFuseOr = 2 };
 
 // links whose loads are in flight while one link's staples are summed
 constexpr int kHbAhead = 1, kOrAhead = 1;
-
-constexpr long long kLinkNone = (long long)0x8000000000000000ull;   // no free candidate within the cap
 
 __device__ __forceinline__ int find_lat_site(const LatTable& lt, int b) {
     int li = 0;
@@ -566,130 +563,7 @@ __global__ __launch_bounds__(kBlock, (HbWaves<T, LPT, VAR>::value)) void k_hb(La
     hb_block<T, MU, LPT, VAR>(lt, th, s, parity, mode, kind, k0, k1, reverse ? (int)gridDim.x - 1 - b0 : b0);
 }
 
-// ---------------------------------------------------------------------------
-// Heatbath class pass under the per-link constraint (Sec. 2.4: the energy
-// restriction imposed when each new angle is generated).  The links of the
-// class are taken one after another in half-index order, each from its
-// conditional restricted to the values that keep the running energy in
-// [lo, hi], and the energy is carried from link to link.  Links of one class
-// share no plaquette, so only that energy couples them.  Per link: the first
-// of the class heatbath's own attempts (same counters) that passes the
-// sampler test AND keeps E inside; if none of the 64 does, the exact arc
-// sampler (attempts 64..127 of the counter's attempt field): on
-// x = |X| in [acos u_hi, acos u_lo], where the window on cos X is [u_lo, u_hi],
-// exp(k cos x) lies under exp(k u_hi - lam (x - x_a)) with
-// lam = k min(sin x_a, (u_hi - u_lo)/(x_b - x_a)), since the secant slope of
-// cos from x_a is the mean of sin over [x_a, x], smallest at an end of the
-// arc; x comes from that truncated exponential, is kept with probability
-// exp(k (cos x - u_hi) + lam (x - x_a)), and its sign is a fair bit.
-//
-// The candidate pre-pass (k_hb<..., kHbPre>, mode kModeLinkPre) has
-// written, per class link, the free heatbath candidate into the alternate
-// plane, its Delta E in the walk's fixed point, and the link's staples and
-// old angle.  That candidate is the first attempt passing the sampler test;
-// it is the constrained draw whenever it keeps E inside.  The walk (one
-// wavefront per chain, the block's other wavefronts staging the next tile of
-// candidates in LDS) scans the candidates in order, 1024 at a time:
-// wavefront prefix sums of Delta E give the running E before every link, the
-// first link whose candidate leaves [lo, hi] is re-drawn (attempt j on lane
-// j, then arc attempt i on lane i; the lowest successful lane wins, which is
-// the first success in attempt order), and the rest of the step is checked
-// again with its running sums shifted by that link's change of Delta E.  E
-// is carried exactly in fixed point (12 bits finer than the class sums), so
-// the result does not depend on the scan's blocking.
-// ---------------------------------------------------------------------------
-constexpr int kWalkTile = 2048;          // class links staged in LDS per tile
-constexpr int kWalkPer = 16;             // links per lane per scan step (1024 per step)
-
-__device__ __forceinline__ long long fx_bound(double v) {
-    return v > 4.0e18 ? 4000000000000000000ll : (v < -4.0e18 ? -4000000000000000000ll : (long long)v);
-}
-
-// Re-draw class link h with the running sum Ssum before it (whole wavefront;
-// staples and old angle from LDS).  Returns the link's fixed-point Delta E
-// on every lane and writes its new angle into the alternate plane.
-template <typename T>
-__device__ __forceinline__ long long link_redraw(const LatDev& L, T* palt, uint32_t h, T C, T S, T t_old, int colour,
-                                                 int kind, uint32_t sweep, uint32_t c3, uint32_t k0, uint32_t k1,
-                                                 double a, double fxw, double Erun, double lo, double hi,
-                                                 long long Ssum, long long lo_fx, long long hi_fx, unsigned& arcs) {
-    using M = Math<T>;
-    const int lane = threadIdx.x & 63;
-    T so, co;
-    M::sincos_rad(t_old, &so, &co);
-    const T eps_old = fms2(C, co, S, so);
-    const T R = M::sqrt_(fma2(C, C, S, S));
-    const T kap = (T)a * R;
-    const T ak = kap < T(0) ? -kap : kap;
-    T q, rm1, kg2;
-    vm_constants(ak, q, rm1, kg2);
-    // the sampler's attempts, attempt j = lane on this lane
-    const uint32_t c1base = ctr1_word(0, (uint32_t)colour, (uint32_t)kind, (uint32_t)L.lat_id);
-    const uint4 w = philox10(make_uint4(h, c1base | (uint32_t)(lane >> 1), sweep, c3), k0, k1);
-    T ch = T(1), sh = T(0);
-    bool acc;
-    if (ak == T(0)) {
-        acc = lane == 0;
-        M::sincos_halfpi_w(w.x, &sh, &ch);
-    } else {
-        acc = (lane & 1) ? vm_attempt(w.z, w.w, q, rm1, kg2, ch, sh) : vm_attempt(w.x, w.y, q, rm1, kg2, ch, sh);
-    }
-    T t_c = t_old, dE_c = T(0);
-    long long d_c = 0;
-    bool ok = false;
-    if (acc) {
-        hb_new_angle(ch, sh, C, S, R, kap, eps_old, t_c, dE_c);
-        d_c = link_fixed(dE_c, L);
-        ok = Ssum + d_c >= lo_fx && Ssum + d_c <= hi_fx;
-    }
-    const unsigned long long m1 = __ballot(ok);
-    if (m1) {
-        const int f = __ffsll((long long)m1) - 1;
-        if (lane == f) st_plane(palt, h, t_c);
-        return __shfl(d_c, f, 64);
-    }
-    // exact arc sampler, in FP64 for either state precision
-    const double Rd = (double)R, kd = (double)kap, akd = (double)ak, ed = (double)eps_old;
-    const double Aw = lo - (Erun - ed), Bw = hi - (Erun - ed);
-    double ulo = -1.0, uhi = 1.0;
-    if (Rd > 0.0) {
-        ulo = fmin(1.0, fmax(-1.0, kd < 0.0 ? -Bw / Rd : Aw / Rd));
-        uhi = fmin(1.0, fmax(-1.0, kd < 0.0 ? -Aw / Rd : Bw / Rd));
-    }
-    const double xa = acos(uhi), xb = acos(ulo), W = xb - xa;
-    bool ok2 = false;
-    double t2 = 0.0;
-    long long d2 = 0;
-    if (W > 0.0) {
-        const double lam = akd * fmin(sin(xa), (uhi - ulo) / W);
-        const uint4 v = philox10(
-            make_uint4(h, ctr1_word((uint32_t)(64 + lane), (uint32_t)colour, (uint32_t)kind, (uint32_t)L.lat_id),
-                       sweep, c3), k0, k1);
-        const double V = (double)M::unif(v.x), U = (double)M::unif(v.y);
-        const double Tt = lam * W < 1e-12 ? V * W : -log1p(V * expm1(-lam * W)) / lam;
-        const double xx = fmin(xa + Tt, xb);
-        if (log(U) <= akd * (cos(xx) - uhi) + lam * Tt) {
-            const double X = (v.z >> 31) ? -xx : xx;
-            const double sg = kd < 0.0 ? -1.0 : 1.0;
-            double sx, cx;
-            sincos(X, &sx, &cx);
-            const double Cd = (double)C, Sd = (double)S;
-            t2 = atan2(sg * (sx * Cd - cx * Sd), sg * (cx * Cd + sx * Sd));
-            if (t2 >= 3.14159265358979323846) t2 -= 6.28318530717958647692;
-            d2 = __double2ll_rn((sg * Rd * cx - ed) * fxw);
-            ok2 = Ssum + d2 >= lo_fx && Ssum + d2 <= hi_fx;
-        }
-    }
-    const unsigned long long m2 = __ballot(ok2);
-    if (m2) {
-        const int f = __ffsll((long long)m2) - 1;
-        if (lane == f) st_plane(palt, h, (T)t2);
-        ++arcs;
-        return __shfl(d2, f, 64);
-    }
-    if (lane == 0) st_plane(palt, h, t_old);
-    return 0;
-}
+constexpr int kWalkTile = 2048;          // class links of the per-link walk staged in LDS per tile
 
 // Stage tile k of a chain's candidates (Delta E, staples, old angle) into LDS
 // buffer `buf`, by threads [first, first + count) of the block; every thread
@@ -729,13 +603,10 @@ __device__ __forceinline__ void walk_stage(const DevState& s, size_t jb, uint32_
     }
 }
 
-// One block per chain.  The walk is a chain of dependent steps and runs on
-// wavefront 0 alone (no barriers inside a tile; the first link whose
-// candidate leaves the window is found with one ballot, since lane l owns
-// links 16 l .. 16 l + 15 of the step; after a re-draw only the entries
-// after it are checked again, with their running sums shifted by the change
-// of that link's Delta E), while wavefronts 1-3 stage the next tile into the
-// other LDS buffer.
+// One block per chain.  The candidate pre-pass (k_hb<..., kHbPre>, mode
+// kModeLinkPre) has written the candidates to the alternate plane and to the link
+// buffers; the walk runs on wavefront 0 alone, with no barriers inside a tile,
+// while wavefronts 1-3 stage the next tile into the other LDS buffer.
 template <typename T, int MU>
 __global__ __launch_bounds__(kBlock) void k_link_walk(LatTable lt, T* __restrict__ th, DevState s, int parity, int kind,
                                                       uint32_t k0, uint32_t k1) {
@@ -759,90 +630,25 @@ __global__ __launch_bounds__(kBlock) void k_link_walk(LatTable lt, T* __restrict
         const int own = (int)((curw >> (8 * colour)) & 1ull);
         T* palt = chain + (size_t)((own ^ 1) * 8 + colour) * L.V2;
         const int gi = s.itv[g];
-        const double a = s.a[gi];
         const double E0 = s.E[g];
-        const double lo = s.lo[gi], hi = s.hi[gi];
-        const double fxw = L.fx * (double)(1 << kWalkBits), fxwinv = L.fxinv / (double)(1 << kWalkBits);
-        const long long lo_fx = fx_bound(ceil((lo - E0) * fxw)), hi_fx = fx_bound(floor((hi - E0) * fxw));
-        const uint32_t sweep = *s.sweep_ctr;
-        const uint32_t c3 = (uint32_t)(gi - L.itv0);
-        long long Ssum = 0;
-        unsigned fixes = 0, arcs = 0;
+        Walk w = walk_begin(L, colour, kind, *s.sweep_ctr, (uint32_t)(gi - L.itv0), k0, k1, s.a[gi], E0, s.lo[gi],
+                            s.hi[gi]);
         for (int k = 0; k < ntiles; ++k) {
             const int buf = k & 1;
             const uint32_t t0 = (uint32_t)k * kWalkTile;
             const int nt = (int)min((uint32_t)kWalkTile, L.V2 - t0);
-            const long long* sd = s_d[buf];
-            int j0 = 0;
-            while (j0 < nt) {
-                // one step: candidates j0 .. j0 + 1023, lane l owning 16 l .. 16 l + 15
-                const int e0 = j0 + kWalkPer * lane;
-                long long dv[kWalkPer], loc = 0;
-                unsigned none = 0;   // entries without a free candidate
-#pragma unroll
-                for (int q = 0; q < kWalkPer; ++q) {
-                    dv[q] = e0 + q < nt ? sd[e0 + q] : 0;
-                    if (dv[q] == kLinkNone) {
-                        dv[q] = 0;
-                        none |= 1u << q;
-                    }
-                    loc += dv[q];
-                }
-                long long incl = loc;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const long long v = __shfl_up(incl, off, 64);
-                    if (lane >= off) incl += v;
-                }
-                // running sum before this lane's first entry; a re-draw shifts
-                // it by the same delta for every later entry of the step
-                long long base = Ssum + incl - loc;
-                const long long tot = __shfl(incl, 63, 64);
-                long long shift = 0;
-                int pos = j0;
-                for (;;) {
-                    long long run = base, before = 0;
-                    int bad = -1;
-#pragma unroll
-                    for (int q = 0; q < kWalkPer; ++q) {
-                        const int e = e0 + q;
-                        if (bad >= 0 || e >= nt) continue;
-                        const long long r1 = run + dv[q];
-                        if (e >= pos && (((none >> q) & 1u) || r1 < lo_fx || r1 > hi_fx)) {
-                            bad = e;
-                            before = run;
-                        }
-                        run = r1;
-                    }
-                    const unsigned long long mb = __ballot(bad >= 0);
-                    if (mb == 0) break;
-                    const int f = __ffsll((long long)mb) - 1;
-                    const int b = __shfl(bad, f, 64);
-                    const long long S_b = __shfl(before, f, 64);
-                    const long long d_old = sd[b] == kLinkNone ? 0 : sd[b];
-                    const long long d_new =
-                        link_redraw<T>(L, palt, t0 + (uint32_t)b, s_c[buf][b], s_s[buf][b], s_t[buf][b], colour, kind,
-                                       sweep, c3, k0, k1, a, fxw, E0 + (double)S_b * fxwinv, lo, hi, S_b, lo_fx,
-                                       hi_fx, arcs);
-                    ++fixes;
-                    const long long delta = d_new - d_old;
-                    shift += delta;
-                    if (lane >= f) base += delta;
-                    pos = b + 1;
-                }
-                Ssum += tot + shift;
-                j0 = min(j0 + kWalkPer * 64, nt);
-            }
+            walk_links<T>(L, w, t0, nt, s_d[buf], s_c[buf], s_s[buf], s_t[buf],
+                          [&](uint32_t h, T v) { st_plane(palt, h, v); });
             __syncthreads();   // pairs with the stagers' barrier of this tile
         }
         if (lane == 0) {
-            s.E[g] = E0 + (double)Ssum * fxwinv;
+            s.E[g] = E0 + (double)w.Ssum * w.fxwinv;
             s.cur[8 * g + colour] ^= (uint8_t)1;
             s.bits[g] |= (uint16_t)(1u << colour);
             s.hb_prop[g] += 1ull;
             s.hb_acc[g] += 1ull;
-            s.link_fix[g] += fixes;
-            s.link_arc[g] += arcs;
+            s.link_fix[g] += w.fixes;
+            s.link_arc[g] += w.arcs;
         }
     } else {
         for (int k = 0; k < ntiles; ++k) {

@@ -20,8 +20,11 @@ def _context(llr, lats, prec, order, replica, class_passes):
     ctx = llr.Context(precision=llr.FP32 if prec == "f32" else llr.FP64, device=0)
     ctx.set_params(n_th=3, n_a=9, n_rm=2, seed=77, replica_exchange=replica, overlap=1.0, recompute_every=5,
                    approach_cap=4000)
-    ctx.set_sweep_order({"grouped": llr.SWEEP_GROUPED, "interleaved": llr.SWEEP_INTERLEAVED,
-                         "staggered": llr.SWEEP_STAGGERED}[order])
+    if order == "link":
+        ctx.set_restriction(True)
+    else:
+        ctx.set_sweep_order({"grouped": llr.SWEEP_GROUPED, "interleaved": llr.SWEEP_INTERLEAVED,
+                             "staggered": llr.SWEEP_STAGGERED}[order])
     for L, E_low, dE in lats:
         ctx.add_lattice(L, E_low, dE)
     ctx.bind_state()
@@ -34,7 +37,7 @@ def _state(ctx, n_lat):
     out = [ctx.export_state(i).cpu().numpy() for i in range(n_lat)]
     out += [ctx.get_energy(i)[j] for i in range(n_lat) for j in (0, 1)]
     out += [ctx.get_a(i)[0] for i in range(n_lat)]
-    return out + list(ctx.stats()) + [ctx.health()[1]]
+    return out + list(ctx.stats()) + [ctx.health()[1], *ctx.link_stats()]
 
 
 CASES = [  # lattices (L, chains): one link to several per thread, idle lanes, mixed sizes, more chains than CUs
@@ -47,6 +50,10 @@ CASES = [  # lattices (L, chains): one link to several per thread, idle lanes, m
     ([(8, 5)], "f64", "grouped", True),
     ([(8, 257)], "f32", "grouped", False),
     ([(8, 257)], "f32", "interleaved", True),
+    ([(4, 3)], "f64", "link", True),
+    ([(6, 2)], "f64", "link", False),
+    ([(8, 3), (4, 2)], "f32", "link", False),
+    ([(8, 2)], "f64", "link", False),   # does not fit with its candidates: class passes
 ]
 
 
