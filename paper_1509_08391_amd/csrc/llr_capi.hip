@@ -122,6 +122,7 @@ struct llr_ctx {
     // device staging of small host arrays (grown on demand)
     void* stage = nullptr;
     size_t stage_bytes = 0;
+    char* pin = nullptr;       // pinned host mirror of small transfers (kPinBytes, held until destroy)
     // link-update accounting (llr_get_rates): class passes applied to every
     // chain, counted as they are enqueued or replayed
     bool capturing = false;        // a sweep is being captured into a graph, not run
@@ -153,6 +154,66 @@ static llr_status ensure_stage(llr_ctx* c, size_t bytes) {
     return LLR_OK;
 }
 
+// Transfers of one call: its host inputs are packed into one region at the
+// start of a device buffer and its outputs into a second one behind it, so that
+// each way takes one asynchronous copy through pinned memory.  (A copy from or
+// to the caller's pageable arrays waits for the stream and costs 10 us or more,
+// and the calls have up to seven of them.)  Transfers larger than the pinned
+// buffer are copied piece by piece as before.
+constexpr size_t kPinBytes = (size_t)64 << 10;
+
+struct Xfer {
+    llr_ctx* c;
+    char* dev;
+    bool pinned;
+    size_t used = 0, up = 0;              // bytes laid out; end of the inputs
+    struct Out { void* dst; size_t off, n; };
+    std::vector<Out> outs;
+    hipError_t err = hipSuccess;
+
+    // bytes: of all inputs and outputs together (rounded up to 8 each)
+    Xfer(llr_ctx* cc, void* device, size_t bytes) : c(cc), dev((char*)device), pinned(cc->pin && bytes <= kPinBytes) {}
+    template <typename P>
+    P* in(const P* src, size_t count) {
+        const size_t n = count * sizeof(P), at = used;
+        used += (n + 7) & ~(size_t)7;
+        up = used;
+        if (pinned) memcpy(c->pin + at, src, n);
+        else if (n && err == hipSuccess) err = hipMemcpyAsync(dev + at, src, n, hipMemcpyHostToDevice, c->stream);
+        return (P*)(dev + at);
+    }
+    llr_status upload() {
+        if (pinned && up && err == hipSuccess) err = hipMemcpyAsync(dev, c->pin, up, hipMemcpyHostToDevice, c->stream);
+        return err == hipSuccess ? LLR_OK : fail(LLR_EDEVICE, std::string("upload: ") + hipGetErrorString(err));
+    }
+    // dst may be null (a device result the caller does not want)
+    template <typename P>
+    P* out(P* dst, size_t count) {
+        const size_t n = count * sizeof(P), at = used;
+        used += (n + 7) & ~(size_t)7;
+        if (dst && n) outs.push_back({dst, at, n});
+        return (P*)(dev + at);
+    }
+    // outputs to the host; ends with the stream synchronised
+    llr_status download() {
+        if (pinned) {
+            if (!outs.empty()) {
+                const size_t lo = outs.front().off, hi = outs.back().off + outs.back().n;
+                err = hipMemcpyAsync(c->pin + lo, dev + lo, hi - lo, hipMemcpyDeviceToHost, c->stream);
+            }
+        } else {
+            for (const auto& o : outs)
+                if (err == hipSuccess) err = hipMemcpyAsync(o.dst, dev + o.off, o.n, hipMemcpyDeviceToHost, c->stream);
+        }
+        if (err == hipSuccess) err = hipStreamSynchronize(c->stream);
+        if (err == hipSuccess) err = hipGetLastError();
+        if (err != hipSuccess) return fail(LLR_EDEVICE, std::string("download: ") + hipGetErrorString(err));
+        if (pinned)
+            for (const auto& o : outs) memcpy(o.dst, c->pin + o.off, o.n);
+        return LLR_OK;
+    }
+};
+
 template <typename P>
 static llr_status dalloc(llr_ctx* c, P** p, size_t count) {
     void* q = nullptr;
@@ -163,6 +224,8 @@ static llr_status dalloc(llr_ctx* c, P** p, size_t count) {
     *p = (P*)q;
     return LLR_OK;
 }
+
+constexpr size_t kReportBytes = 3 * 8 + 2 * 4;   // a, E, conv_sweeps, conv_iter, conf per chain
 
 // ceil(2^32 / d) for d >= 2 (divisor 1 is handled by the kernels directly)
 static uint32_t magic(uint32_t d) { return d < 2 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
@@ -303,10 +366,18 @@ static llr_status layout(llr_ctx* c) {
     llr_status st;
 #define AL(field, cnt) \
     if ((st = dalloc(c, &s.field, (cnt))) != LLR_OK) return st;
-    AL(E, n) AL(acc, n) AL(eacc, n) AL(oacc, n) AL(obs, n) AL(cur, 8 * n) AL(itv, n) AL(b, 8 * n) AL(eta, 8 * n)
+    // what get_a and get_energy report, in one block: one copy brings all of it
+    unsigned char* rep = nullptr;
+    if ((st = dalloc(c, &rep, kReportBytes * (size_t)n)) != LLR_OK) return st;
+    s.a = (double*)rep;
+    s.E = s.a + n;
+    s.conv_sweeps = (long long*)(s.E + n);
+    s.conv_iter = (int*)(s.conv_sweeps + n);
+    s.conf = s.conv_iter + n;
+    AL(acc, n) AL(eacc, n) AL(oacc, n) AL(obs, n) AL(cur, 8 * n) AL(itv, n) AL(b, 8 * n) AL(eta, 8 * n)
     AL(sprev, 8 * n) AL(bits, n + 2) AL(bits_last, n + 2) AL(hb_prop, n) AL(hb_acc, n) AL(fu_acc, n) AL(health, n)
-    AL(drift, n) AL(a, n) AL(lo, n) AL(hi, n)
-    AL(cen, n) AL(w, n) AL(sumE, n) AL(conf, n) AL(conv_iter, n) AL(conv_sweeps, n) AL(mu_lnrho, n)
+    AL(drift, n) AL(lo, n) AL(hi, n)
+    AL(cen, n) AL(w, n) AL(sumE, n) AL(mu_lnrho, n)
     AL(mu_b, kMaxLat) AL(link_fix, n) AL(link_arc, n)
     AL(lat_done, kMaxLat) AL(lat_outside, kMaxLat) AL(lat_approach, kMaxLat) AL(sweep_ctr, 1)
     AL(approach_ctr, 1) AL(arrive, 1) AL(rm_iter, 1) AL(re_cnt, 2) AL(bits_row, 1)
@@ -381,19 +452,28 @@ struct TimeScope {
 // The energy recompute's sticky per-chain flags (kHealth*): LLR_ENUMERIC with
 // the first flagged chain named, the flags left set until llr_health clears
 // them.  Called at the end of the calls that run sweeps.
+// Ends with the stream synchronised.
 static llr_status health_check(llr_ctx* c) {
     const int n = c->lt.n_chains;
-    std::vector<uint32_t> f(n);
-    std::vector<double> d(n);
-    HIPCHK(hipMemcpy(f.data(), c->ds.health, 4 * (size_t)n, hipMemcpyDeviceToHost));
+    std::vector<uint32_t> big;
+    const uint32_t* f = (const uint32_t*)c->pin;
+    if (4 * (size_t)n > kPinBytes) {
+        big.resize(n);
+        f = big.data();
+    }
+    HIPCHK(hipMemcpyAsync((void*)f, c->ds.health, 4 * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    HIPCHK(hipGetLastError());
     for (int g = 0; g < n; ++g) {
         if (!f[g]) continue;
-        HIPCHK(hipMemcpy(d.data(), c->ds.drift, 8 * (size_t)n, hipMemcpyDeviceToHost));
+        const uint32_t fg = f[g];
+        double d = 0.0;
+        HIPCHK(hipMemcpy(&d, c->ds.drift + g, 8, hipMemcpyDeviceToHost));
         char msg[256];
         snprintf(msg, sizeof msg, "chain %d failed a health test at an energy recompute:%s%s%s (largest drift %.3e)", g,
-                 (f[g] & kHealthNonFinite) ? " non-finite angle" : "",
-                 (f[g] & kHealthDrift) ? " incremental E drifted beyond the bound" : "",
-                 (f[g] & kHealthOutside) ? " E outside its restriction" : "", d[g]);
+                 (fg & kHealthNonFinite) ? " non-finite angle" : "",
+                 (fg & kHealthDrift) ? " incremental E drifted beyond the bound" : "",
+                 (fg & kHealthOutside) ? " E outside its restriction" : "", d);
         return fail(LLR_ENUMERIC, msg);
     }
     return LLR_OK;
@@ -774,9 +854,9 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
         launch_rm_update(c->lt, c->ds, cfg, c->stream);
         c->rm_done += 1;
     }
+    if (!c->timing) return health_check(c);
     HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    if (c->timing) harvest(c);
+    harvest(c);
     return health_check(c);
 }
 
@@ -847,9 +927,9 @@ static llr_status plain_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, int m
                                           c->stream));
         if (bits) HIPCHK(hipMemcpyAsync(bits + (size_t)t0 * n, dB, 2 * (size_t)m * n, hipMemcpyDeviceToHost, c->stream));
     }
+    if (!c->timing) return health_check(c);
     HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    if (c->timing) harvest(c);
+    harvest(c);
     return health_check(c);
 }
 
@@ -886,7 +966,6 @@ static llr_status observables_impl(llr_ctx* c, int n_meas, int gap, long long sw
         HIPCHK(hipMemcpyAsync(B_out + (size_t)m0 * n, dB, 8 * (size_t)nm * n, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
     }
-    HIPCHK(hipGetLastError());
     if (c->timing) harvest(c);
     return health_check(c);
 }
@@ -926,7 +1005,10 @@ llr_status llr_create(llr_ctx** out, int hip_device, void* hip_stream, int preci
     HIPCHK(hipSetDevice(hip_device));
     const llr_status sst = scratch_setup(hip_device);
     if (sst != LLR_OK) return sst;
+    void* pin = nullptr;
+    HIPCHK(hipHostMalloc(&pin, kPinBytes, hipHostMallocDefault));
     llr_ctx* c = new llr_ctx();
+    c->pin = (char*)pin;
     c->device = hip_device;
     c->stream = (hipStream_t)hip_stream;
     c->precision = precision;
@@ -959,6 +1041,7 @@ void llr_destroy(llr_ctx* c) {
     for (auto e : c->pool) hipEventDestroy(e);
     for (void* p : c->allocs) hipFree(p);
     if (c->stage) hipFree(c->stage);
+    if (c->pin) hipHostFree(c->pin);
     delete c;
 }
 
@@ -1276,19 +1359,39 @@ llr_status llr_recompute_energy(llr_ctx* c) {
     return health_check(c);
 }
 
+}  // extern "C"
+
+// The chains' report block in pinned memory, after all work on the stream; null
+// if it does not fit or could not be copied (the caller then copies piecewise).
+static const char* report(llr_ctx* c) {
+    const size_t bytes = kReportBytes * (size_t)c->lt.n_chains;
+    if (bytes > kPinBytes) return nullptr;
+    if (hipMemcpyAsync(c->pin, c->ds.a, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess) return nullptr;
+    return hipStreamSynchronize(c->stream) == hipSuccess ? c->pin : nullptr;
+}
+static size_t report_off(const llr_ctx* c, const void* p) { return (size_t)((const char*)p - (const char*)c->ds.a); }
+
+extern "C" {
+
 llr_status llr_get_a(llr_ctx* c, int lat, double* a, int* conv_iter, long long* conv_sweeps) {
     if (!c || !c->laid_out) return fail(LLR_ESTATE, "no state");
     if (lat < 0 || lat >= c->lt.n) return fail(LLR_EINVAL, "no such lattice");
     HIPCHK(hipSetDevice(c->device));
     const LatDev& L = c->lt.l[lat];
-    HIPCHK(hipStreamSynchronize(c->stream));
-    if (a) HIPCHK(hipMemcpy(a, c->ds.a + L.chain0, 8 * L.n_chains, hipMemcpyDeviceToHost));
-    if (conv_iter) HIPCHK(hipMemcpy(conv_iter, c->ds.conv_iter + L.chain0, 4 * L.n_chains, hipMemcpyDeviceToHost));
-    if (conv_sweeps) {
-        HIPCHK(hipMemcpy(conv_sweeps, c->ds.conv_sweeps + L.chain0, 8 * L.n_chains, hipMemcpyDeviceToHost));
-        for (int k = 0; k < L.n_chains; ++k)
-            if (conv_sweeps[k] >= 0) conv_sweeps[k] += c->approach_sweeps[lat];
+    const int n = L.n_chains;
+    if (const char* r = report(c)) {
+        if (a) memcpy(a, r + 8 * (size_t)L.chain0, 8 * (size_t)n);
+        if (conv_iter) memcpy(conv_iter, r + report_off(c, c->ds.conv_iter + L.chain0), 4 * (size_t)n);
+        if (conv_sweeps) memcpy(conv_sweeps, r + report_off(c, c->ds.conv_sweeps + L.chain0), 8 * (size_t)n);
+    } else {
+        HIPCHK(hipStreamSynchronize(c->stream));
+        if (a) HIPCHK(hipMemcpy(a, c->ds.a + L.chain0, 8 * (size_t)n, hipMemcpyDeviceToHost));
+        if (conv_iter) HIPCHK(hipMemcpy(conv_iter, c->ds.conv_iter + L.chain0, 4 * (size_t)n, hipMemcpyDeviceToHost));
+        if (conv_sweeps) HIPCHK(hipMemcpy(conv_sweeps, c->ds.conv_sweeps + L.chain0, 8 * (size_t)n, hipMemcpyDeviceToHost));
     }
+    if (conv_sweeps)
+        for (int k = 0; k < n; ++k)
+            if (conv_sweeps[k] >= 0) conv_sweeps[k] += c->approach_sweeps[lat];
     return LLR_OK;
 }
 
@@ -1311,12 +1414,17 @@ llr_status llr_get_energy(llr_ctx* c, int lat, double* E, int* conf) {
     if (lat < 0 || lat >= c->lt.n) return fail(LLR_EINVAL, "no such lattice");
     HIPCHK(hipSetDevice(c->device));
     const LatDev& L = c->lt.l[lat];
-    HIPCHK(hipStreamSynchronize(c->stream));
-    if (E) HIPCHK(hipMemcpy(E, c->ds.E + L.chain0, 8 * L.n_chains, hipMemcpyDeviceToHost));
-    if (conf) {
-        HIPCHK(hipMemcpy(conf, c->ds.conf + L.chain0, 4 * L.n_chains, hipMemcpyDeviceToHost));
-        for (int k = 0; k < L.n_chains; ++k) conf[k] -= L.chain0;
+    const int n = L.n_chains;
+    if (const char* r = report(c)) {
+        if (E) memcpy(E, r + report_off(c, c->ds.E + L.chain0), 8 * (size_t)n);
+        if (conf) memcpy(conf, r + report_off(c, c->ds.conf + L.chain0), 4 * (size_t)n);
+    } else {
+        HIPCHK(hipStreamSynchronize(c->stream));
+        if (E) HIPCHK(hipMemcpy(E, c->ds.E + L.chain0, 8 * (size_t)n, hipMemcpyDeviceToHost));
+        if (conf) HIPCHK(hipMemcpy(conf, c->ds.conf + L.chain0, 4 * (size_t)n, hipMemcpyDeviceToHost));
     }
+    if (conf)
+        for (int k = 0; k < n; ++k) conf[k] -= L.chain0;
     return LLR_OK;
 }
 
@@ -1528,25 +1636,37 @@ llr_status llr_reconstruct(llr_ctx* c, const double* centres, const double* a, i
     if (!c || !centres || !a || n < 1 || nb < 0 || !(s > 0) || !(six_v > 0)) return fail(LLR_EINVAL, "bad argument");
     if (nb > 0 && (!beta || !u_mean || !cv)) return fail(LLR_EINVAL, "bad beta arrays");
     HIPCHK(hipSetDevice(c->device));
-    llr_status st = ensure_stage(c, 8 * (size_t)(3 * n + 3 * nb) + 64);
+    const size_t bytes = 8 * (3 * (size_t)n + 3 * (size_t)nb);
+    llr_status st = ensure_stage(c, bytes + 64);
     if (st != LLR_OK) return st;
-    double* dc = (double*)c->stage;
-    double* da = dc + n;
-    double* dl = da + n;
-    double* db = dl + n;
-    double* du = db + nb;
-    double* dv = du + nb;
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(da, a, 8 * n, hipMemcpyHostToDevice, c->stream));
-    if (nb) HIPCHK(hipMemcpyAsync(db, beta, 8 * nb, hipMemcpyHostToDevice, c->stream));
+    Xfer x(c, c->stage, bytes);
+    const double* dc = x.in(centres, n);
+    const double* da = x.in(a, n);
+    const double* db = x.in(beta, nb);
+    double* dl = x.out(ln_rho, n);
+    double* du = x.out(u_mean, nb);
+    double* dv = x.out(cv, nb);
+    if ((st = x.upload()) != LLR_OK) return st;
     launch_recon(dc, da, n, s, six_v, db, nb, dl, du, dv, c->stream);
-    if (ln_rho) HIPCHK(hipMemcpyAsync(ln_rho, dl, 8 * n, hipMemcpyDeviceToHost, c->stream));
-    if (nb) {
-        HIPCHK(hipMemcpyAsync(u_mean, du, 8 * nb, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipMemcpyAsync(cv, dv, 8 * nb, hipMemcpyDeviceToHost, c->stream));
-    }
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
+    return x.download();
+}
+
+// beta_c and the peak with all device data at `base` (3 n + ng + 8 doubles)
+static llr_status beta_c_in(llr_ctx* c, double* base, const double* centres, const double* a, int n, double s,
+                            double six_v, double blo, double bhi, double h, double tol, double* beta_c,
+                            double* cv_peak) {
+    double r[2];
+    Xfer x(c, base, 8 * (2 * (size_t)n + 2));
+    const double* dc = x.in(centres, n);
+    const double* da = x.in(a, n);
+    double* out = x.out(r, 2);
+    const llr_status st = x.upload();
+    if (st != LLR_OK) return st;
+    launch_beta_c(dc, da, n, s, six_v, blo, bhi, h, tol, base + 2 * (size_t)n + 4, out, c->stream);
+    const llr_status sd = x.download();
+    if (sd != LLR_OK) return sd;
+    *beta_c = r[0];
+    *cv_peak = r[1];
     return LLR_OK;
 }
 
@@ -1560,20 +1680,7 @@ llr_status llr_beta_c(llr_ctx* c, const double* centres, const double* a, int n,
     HIPCHK(hipSetDevice(c->device));
     llr_status st = ensure_stage(c, 8 * (size_t)(3 * n + ng + 8) + 64);
     if (st != LLR_OK) return st;
-    double* dc = (double*)c->stage;
-    double* da = dc + n;
-    double* out = da + n;
-    double* scr = out + 4;
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(da, a, 8 * n, hipMemcpyHostToDevice, c->stream));
-    launch_beta_c(dc, da, n, s, six_v, blo, bhi, h, tol, scr, out, c->stream);
-    double r[2];
-    HIPCHK(hipMemcpyAsync(r, out, 16, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    *beta_c = r[0];
-    *cv_peak = r[1];
-    return LLR_OK;
+    return beta_c_in(c, (double*)c->stage, centres, a, n, s, six_v, blo, bhi, h, tol, beta_c, cv_peak);
 }
 
 llr_status llr_beta_c_noalloc(llr_ctx* c, const double* centres, const double* a, int n, double s, double six_v,
@@ -1590,20 +1697,7 @@ llr_status llr_beta_c_noalloc(llr_ctx* c, const double* centres, const double* a
     void* base = (c->device >= 0 && c->device < kMaxDevices) ? g_scratch_ptr[c->device] : nullptr;
     if (!base) return fail(LLR_ESTATE, "no fixed device buffer for this context's device");
     HIPCHK(hipSetDevice(c->device));
-    double* dc = (double*)base;
-    double* da = dc + n;
-    double* out = da + n;
-    double* scr = out + 4;
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(da, a, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    launch_beta_c(dc, da, n, s, six_v, blo, bhi, h, tol, scr, out, c->stream);
-    double r[2];
-    HIPCHK(hipMemcpyAsync(r, out, 16, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    *beta_c = r[0];
-    *cv_peak = r[1];
-    return LLR_OK;
+    return beta_c_in(c, (double*)base, centres, a, n, s, six_v, blo, bhi, h, tol, beta_c, cv_peak);
 }
 
 static bool uniform_centres(const double* c, int n, double s) {
@@ -1629,25 +1723,19 @@ llr_status llr_obs_reconstruct(llr_ctx* c, const double* centres, const double* 
     if (!uniform_centres(centres, n, s)) return fail(LLR_EINVAL, "centres must be spaced by s");
     HIPCHK(hipSetDevice(c->device));
     const size_t mn = (size_t)m * n;
-    llr_status st = ensure_stage(c, 8 * (2 * mn + 3 * (size_t)n + 2 * (size_t)nb) + 64);
+    const size_t bytes = 8 * (2 * mn + 2 * (size_t)n + 2 * (size_t)nb);
+    llr_status st = ensure_stage(c, bytes + 8 * (size_t)n + 64);
     if (st != LLR_OK) return st;
-    double* dE = (double*)c->stage;
-    double* dB = dE + mn;
-    double* dc = dB + mn;
-    double* da = dc + n;
-    double* dL = da + n;
-    double* db = dL + n;
-    double* dout = db + nb;
-    HIPCHK(hipMemcpyAsync(dE, E, 8 * mn, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(dB, B, 8 * mn, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(da, a, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(db, beta, 8 * (size_t)nb, hipMemcpyHostToDevice, c->stream));
-    launch_obs_bracket(dE, dB, m, dc, da, n, s, db, nb, dout, dL, c->stream);
-    HIPCHK(hipMemcpyAsync(B_mean, dout, 8 * (size_t)nb, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    return LLR_OK;
+    Xfer x(c, c->stage, bytes);
+    const double* dE = x.in(E, mn);
+    const double* dB = x.in(B, mn);
+    const double* dc = x.in(centres, n);
+    const double* da = x.in(a, n);
+    const double* db = x.in(beta, nb);
+    double* dout = x.out(B_mean, nb);
+    if ((st = x.upload()) != LLR_OK) return st;
+    launch_obs_bracket(dE, dB, m, dc, da, n, s, db, nb, dout, dout + nb, c->stream);
+    return x.download();
 }
 
 llr_status llr_muca_begin(llr_ctx* c, const double* b) {
@@ -1690,27 +1778,20 @@ llr_status llr_muca_reweight(llr_ctx* c, const double* E, long m, const double* 
         return fail(LLR_EINVAL, "bad argument");
     if (!uniform_centres(centres, n, s)) return fail(LLR_EINVAL, "centres must be spaced by s");
     HIPCHK(hipSetDevice(c->device));
-    llr_status st = ensure_stage(c, 8 * ((size_t)m + 3 * (size_t)n + 3 * (size_t)nb) + 64);
+    const size_t bytes = 8 * ((size_t)m + 2 * (size_t)n + 3 * (size_t)nb);
+    llr_status st = ensure_stage(c, bytes + 8 * (size_t)n + 64);
     if (st != LLR_OK) return st;
-    double* dE = (double*)c->stage;
-    double* dc = dE + m;
-    double* da = dc + n;
-    double* dL = da + n;
-    double* db = dL + n;
-    double* du = db + nb;
-    double* dv = du + nb;
-    HIPCHK(hipMemcpyAsync(dE, E, 8 * (size_t)m, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(da, a, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(db, beta, 8 * (size_t)nb, hipMemcpyHostToDevice, c->stream));
-    launch_reweight(dE, m, dc, da, n, s, db, nb, six_v, du, dv, dL, c->stream);
-    HIPCHK(hipMemcpyAsync(u_mean, du, 8 * (size_t)nb, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(cv, dv, 8 * (size_t)nb, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    return LLR_OK;
+    Xfer x(c, c->stage, bytes);
+    const double* dE = x.in(E, (size_t)m);
+    const double* dc = x.in(centres, n);
+    const double* da = x.in(a, n);
+    const double* db = x.in(beta, nb);
+    double* du = x.out(u_mean, nb);
+    double* dv = x.out(cv, nb);
+    if ((st = x.upload()) != LLR_OK) return st;
+    launch_reweight(dE, m, dc, da, n, s, db, nb, six_v, du, dv, dv + nb, c->stream);
+    return x.download();
 }
-
 
 llr_status llr_prob_density(llr_ctx* c, const double* centres, const double* a, int n, double s, double beta,
                             const double* E, int m, double* log_p) {
@@ -1718,21 +1799,17 @@ llr_status llr_prob_density(llr_ctx* c, const double* centres, const double* a, 
         return fail(LLR_EINVAL, "bad argument");
     if (!uniform_centres(centres, n, s)) return fail(LLR_EINVAL, "centres must be spaced by s");
     HIPCHK(hipSetDevice(c->device));
-    llr_status st = ensure_stage(c, 8 * (size_t)(3 * n + 2 * m + 4) + 64);
+    const size_t bytes = 8 * (2 * (size_t)n + 2 * (size_t)m);
+    llr_status st = ensure_stage(c, bytes + 8 * ((size_t)n + 4) + 64);
     if (st != LLR_OK) return st;
-    double* dc = (double*)c->stage;
-    double* da = dc + n;
-    double* dE = da + n;
-    double* dp = dE + m;
-    double* scr = dp + m;
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(da, a, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    if (m) HIPCHK(hipMemcpyAsync(dE, E, 8 * (size_t)m, hipMemcpyHostToDevice, c->stream));
-    launch_prob(dc, da, n, s, beta, dE, m, dp, 0, nullptr, nullptr, nullptr, scr, c->stream);
-    if (m) HIPCHK(hipMemcpyAsync(log_p, dp, 8 * (size_t)m, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
-    return LLR_OK;
+    Xfer x(c, c->stage, bytes);
+    const double* dc = x.in(centres, n);
+    const double* da = x.in(a, n);
+    const double* dE = x.in(E, m);
+    double* dp = x.out(log_p, m);
+    if ((st = x.upload()) != LLR_OK) return st;
+    launch_prob(dc, da, n, s, beta, dE, m, dp, 0, nullptr, nullptr, nullptr, dp + m, c->stream);
+    return x.download();
 }
 
 llr_status llr_prob_peaks(llr_ctx* c, const double* centres, const double* a, int n, double s, double beta,
@@ -1742,26 +1819,26 @@ llr_status llr_prob_peaks(llr_ctx* c, const double* centres, const double* a, in
         return fail(LLR_EINVAL, "bad argument");
     if (!uniform_centres(centres, n, s)) return fail(LLR_EINVAL, "centres must be spaced by s");
     HIPCHK(hipSetDevice(c->device));
-    llr_status st = ensure_stage(c, 8 * (size_t)(3 * n + 2 * max_peaks + 8) + 64);
+    const size_t bytes = 8 * (2 * (size_t)n + 2 * (size_t)max_peaks + 1);
+    llr_status st = ensure_stage(c, bytes + 8 * ((size_t)n + 2) + 64);
     if (st != LLR_OK) return st;
-    double* dc = (double*)c->stage;
-    double* da = dc + n;
-    double* dEp = da + n;
-    double* dlp = dEp + max_peaks;
-    int* dn = (int*)(dlp + max_peaks);
-    double* scr = dlp + max_peaks + 2;
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(da, a, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    launch_prob(dc, da, n, s, beta, nullptr, 0, nullptr, max_peaks, dEp, dlp, dn, scr, c->stream);
+    // only the peaks found are written to the caller's arrays
+    std::vector<double> pk(2 * (size_t)max_peaks);
     int nf = 0;
-    HIPCHK(hipMemcpyAsync(&nf, dn, 4, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+    Xfer x(c, c->stage, bytes);
+    const double* dc = x.in(centres, n);
+    const double* da = x.in(a, n);
+    int* dn = x.out(&nf, 1);
+    double* dEp = x.out(pk.data(), max_peaks);
+    double* dlp = x.out(pk.data() + max_peaks, max_peaks);
+    if ((st = x.upload()) != LLR_OK) return st;
+    launch_prob(dc, da, n, s, beta, nullptr, 0, nullptr, max_peaks, dEp, dlp, dn, dlp + max_peaks, c->stream);
+    if ((st = x.download()) != LLR_OK) return st;
     const int keep = std::min(nf, max_peaks);
     if (keep > 0) {
-        HIPCHK(hipMemcpy(E_peak, dEp, 8 * (size_t)keep, hipMemcpyDeviceToHost));
-        HIPCHK(hipMemcpy(log_p_peak, dlp, 8 * (size_t)keep, hipMemcpyDeviceToHost));
+        memcpy(E_peak, pk.data(), 8 * (size_t)keep);
+        memcpy(log_p_peak, pk.data() + max_peaks, 8 * (size_t)keep);
     }
-    HIPCHK(hipGetLastError());
     *n_found = nf;
     return LLR_OK;
 }
@@ -1775,22 +1852,20 @@ llr_status llr_bootstrap(llr_ctx* c, const double* centres, const double* a_runs
     const long ng = (long)std::floor((bhi - blo) / h + 0.5);
     if (ng > 1000000 || (double)n_boot * (double)(ng + 1) > 6.5e7) return fail(LLR_EINVAL, "beta grid too fine");
     HIPCHK(hipSetDevice(c->device));
-    const size_t nd = (size_t)n * (1 + (size_t)n_runs + 2 * (size_t)n_boot) + (size_t)n_boot * (ng + 1 + 2) + 8;
-    llr_status st = ensure_stage(c, 8 * nd + 64);
+    const size_t bytes = 8 * ((size_t)n * (1 + (size_t)n_runs) + 2 * (size_t)n_boot);
+    llr_status st = ensure_stage(c, bytes + 8 * (2 * (size_t)n * n_boot + (size_t)n_boot * (ng + 1) + 8) + 64);
     if (st != LLR_OK) return st;
-    double* dc = (double*)c->stage;
-    double* druns = dc + n;
-    double* dbar = druns + (size_t)n_runs * n;
-    double* dout = dbar + (size_t)n_boot * n;
-    double* scr = dout + 2 * (size_t)n_boot;
-    HIPCHK(hipMemcpyAsync(dc, centres, 8 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(druns, a_runs, 8 * (size_t)n * n_runs, hipMemcpyHostToDevice, c->stream));
+    std::vector<double> r(2 * (size_t)n_boot);
+    Xfer x(c, c->stage, bytes);
+    const double* dc = x.in(centres, n);
+    const double* druns = x.in(a_runs, (size_t)n * n_runs);
+    double* dout = x.out(r.data(), r.size());
+    double* dbar = dout + r.size();
+    double* scr = dbar + (size_t)n_boot * n;
+    if ((st = x.upload()) != LLR_OK) return st;
     launch_boot_mean(druns, n_runs, n, n_boot, seed, dbar, c->stream);
     launch_beta_c_rows(dc, dbar, n, n_boot, s, six_v, blo, bhi, h, tol, scr, dout, c->stream);
-    std::vector<double> r(2 * (size_t)n_boot);
-    HIPCHK(hipMemcpyAsync(r.data(), dout, 16 * (size_t)n_boot, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipGetLastError());
+    if ((st = x.download()) != LLR_OK) return st;
     for (int b = 0; b < n_boot; ++b) {
         beta_c[b] = r[2 * b];
         cv_peak[b] = r[2 * b + 1];
@@ -1900,6 +1975,16 @@ static llr_status stage_inputs(llr_ctx* c, const float* w, const float* u, const
     *du = (float*)p; p += 4 * (size_t)n;
     *dl = (float*)p; p += 4 * (size_t)n; p = (char*)(((uintptr_t)p + 15) & ~(uintptr_t)15);
     *dA = (double*)p;
+    const size_t bytes = (size_t)((char*)(*dA + (a ? n : 0)) - (char*)c->stage);
+    if (bytes <= kPinBytes) {   // one copy, as Xfer's
+        const auto at = [&](const void* d) { return c->pin + ((const char*)d - (const char*)c->stage); };
+        memcpy(at(*dw), w, 4 * kMlpNP);
+        memcpy(at(*du), u, 4 * (size_t)n);
+        memcpy(at(*dl), invL, 4 * (size_t)n);
+        if (a) memcpy(at(*dA), a, 8 * (size_t)n);
+        HIPCHK(hipMemcpyAsync(c->stage, c->pin, bytes, hipMemcpyHostToDevice, c->stream));
+        return LLR_OK;
+    }
     HIPCHK(hipMemcpyAsync(*dw, w, 4 * kMlpNP, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(*du, u, 4 * (size_t)n, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(*dl, invL, 4 * (size_t)n, hipMemcpyHostToDevice, c->stream));
