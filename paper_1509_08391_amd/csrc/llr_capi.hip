@@ -111,7 +111,7 @@ struct llr_ctx {
     hipGraphExec_t sweep_graph[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     hipStream_t cap_stream = nullptr;  // default priority
     hipStream_t side = nullptr;        // staggered order: the second chain set's stream (default priority)
-    hipEvent_t fork_ev = nullptr, join_ev = nullptr;
+    hipEvent_t fork_ev = nullptr, join_ev = nullptr, half_ev = nullptr;
     bool rm_open = false;
     // timing
     bool timing = false;
@@ -308,6 +308,13 @@ static void half_tables(const LatTable& lt, LatTable& a, LatTable& b) {
     }
     set_tiles(a, lt.hb_lpt, lt.or_lpt);
     set_tiles(b, lt.hb_lpt, lt.or_lpt);
+    for (LatTable* t : {&a, &b}) {   // site kernels on the halves
+        t->site_blocks = 0;
+        for (int i = 0; i < t->n; ++i) {
+            t->l[i].eblock0 = t->site_blocks;
+            t->site_blocks += t->l[i].n_chains * t->l[i].ebpc;
+        }
+    }
 }
 
 static llr_status layout(llr_ctx* c) {
@@ -540,6 +547,8 @@ static void enqueue_chain(llr_ctx* c, const ChainArgs& a) {
 }
 // sweeps of one chain-resident launch: bounds a launch's duration
 constexpr int kChainSweeps = 64;
+// class links from which sweeps run in two pipelined halves (pipelined_sweeps)
+constexpr long long kPipeLinks = 900000;
 
 // one restricted sweep of all chains, then recompute / replica exchange /
 // measurement; E_row, b_row: device rows for the sweep's E and accept bits
@@ -600,6 +609,100 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
 }
 
 static llr_status ensure_link_buffers(llr_ctx* c);
+static llr_status ensure_side_stream(llr_ctx* c);
+
+// Whether grouped (and staggered) sweeps of this mode run with the chains in two
+// halves on two streams.  The heatbath passes are bound by vector instructions and the
+// overrelaxation passes by memory, and a chain's overrelaxation passes neither
+// change its E nor depend on its interval label: the end of a sweep (replica
+// exchange, measurement, counters) only needs every chain's heatbath passes.  So
+// while one half runs its overrelaxation the other runs its heatbath, half a
+// sweep later, with the sequence of every chain, and so every result, unchanged.
+// (Staggered sweeps have the half sweep between the halves already, and need no
+// more than this of a join.)  Half launches leave less work to hide their ramps
+// and are twice as many: below kPipeLinks class links (FP64 ones count twice) whole
+// launches from captured graphs are as fast or faster.  Measured, us per sweep
+// whole / halves, FP32: L = 20 x 128 1244 / 1175, 18 x 96 639 / 585, 16 x 64 333 /
+// 292, 12 x 96 (1.0 M links) 226 / 198, 14 x 48 (0.92 M) 214 / 208, 18 x 16 (0.84 M)
+// 210 / 239, 10 x 160 (0.8 M) 193 / 193, 12 x 64 (0.66 M) 177 / 190; FP64: 12 x 64
+// 408 / 360, 12 x 32 (0.33 M) 272 / 276, 14 x 16 (0.31 M) 270 / 278, 10 x 32 198 / 201.
+// (One captured graph per period of sweeps made the halves slower: 1198 us at
+// L = 20 x 128.)
+static bool pipelined_sweeps(const llr_ctx* c, int mode) {
+    if (!plain_mode(mode) || c->interleave || c->timing || !c->use_graphs || resident_sweeps(c, mode))
+        return false;
+    long long links = 0;
+    bool two = false;
+    for (int i = 0; i < c->lt.n; ++i) {
+        links += (long long)c->lt.l[i].n_chains * c->lt.l[i].V2;
+        two = two || c->lt.l[i].n_chains > 1;
+    }
+    return two && links * (c->precision == LLR_FP32 ? 1 : 2) >= kPipeLinks;
+}
+
+// A run of sweeps: recompute E after sweep j0 + t where every divides its index
+// + 1 and after `last`; accumulate E from sweep t = measure_from on.
+struct SweepRun {
+    int n, j0, every, last, measure_from;
+    bool replica;
+    double* E_hist;       // optional device rows per sweep
+    uint16_t* bits_hist;
+    bool recompute(int t) const { return every > 0 && ((j0 + t + 1) % every == 0 || j0 + t == last); }
+};
+
+template <typename T>
+static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
+    llr_status st = ensure_side_stream(c);
+    if (st != LLR_OK) return st;
+    LatTable ha, hb;
+    half_tables(c->lt, ha, hb);
+    const uint32_t k0 = (uint32_t)c->prm.seed, k1 = (uint32_t)(c->prm.seed >> 32);
+    T* th = (T*)c->state;
+    const int check = recompute_check(mode), n = c->lt.n_chains;
+    const auto heat = [&](const LatTable& t, hipStream_t s) {
+        for (int col = 0; col < 8; ++col) launch_hb_pass<T>(t, th, c->ds, col, mode, kSweep, k0, k1, s);
+    };
+    const auto relax = [&](const LatTable& t, hipStream_t s) {
+        for (int col = 0; col < 8; ++col) launch_or_pass<T>(t, th, c->ds, col, 0, s);
+    };
+    const bool relax_first = c->stagger;   // the second half's sweep starts with its overrelaxation
+    for (int t = 0; t < r.n; ++t) {
+        const bool rec = r.recompute(t);
+        if (!relax_first) heat(ha, c->stream);
+        if (t == 0) {   // grouped: the second half starts half a sweep later
+            HIPCHK(hipEventRecord(c->fork_ev, c->stream));
+            HIPCHK(hipStreamWaitEvent(c->side, c->fork_ev, 0));
+        }
+        if (relax_first) {
+            relax(hb, c->side);
+            heat(ha, c->stream);
+        }
+        if (rec) {
+            relax(ha, c->stream);
+            launch_energy<T>(ha, th, c->ds, c->stream, false, check);
+        }
+        HIPCHK(hipEventRecord(c->half_ev, c->stream));   // E of the first half is final for this sweep
+        if (!rec) relax(ha, c->stream);
+        heat(hb, c->side);
+        if (rec) {
+            if (!relax_first) relax(hb, c->side);
+            launch_energy<T>(hb, th, c->ds, c->side, false, check);
+        }
+        HIPCHK(hipStreamWaitEvent(c->side, c->half_ev, 0));
+        if (r.replica) launch_replica(c->lt, c->ds, k0, k1, c->side);
+        launch_end_sweep(c->lt, c->ds, t >= r.measure_from ? 1 : 0, 0, 1, r.E_hist ? r.E_hist + (size_t)t * n : nullptr,
+                         r.bits_hist ? r.bits_hist + (size_t)t * n : nullptr, c->side);
+        HIPCHK(hipEventRecord(c->join_ev, c->side));
+        if (!rec && !relax_first) relax(hb, c->side);
+        // the first half's next sweep needs the labels and counters, not the second half's overrelaxation
+        HIPCHK(hipStreamWaitEvent(c->stream, c->join_ev, 0));
+        note_sweep(c, false);
+        if ((t & 127) == 127) HIPCHK(hipStreamSynchronize(c->side));   // bound the queue depth
+    }
+    HIPCHK(hipEventRecord(c->join_ev, c->side));
+    HIPCHK(hipStreamWaitEvent(c->stream, c->join_ev, 0));
+    return LLR_OK;
+}
 
 // the heatbath mode of Algorithm 1's restricted sweeps
 static int restricted_mode(const llr_ctx* c) { return c->per_link ? LLR_MODE_LINK : LLR_MODE_RESTRICTED; }
@@ -835,6 +938,7 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
     llr_status st = LLR_OK;
     // without replica exchange nothing couples the chains between sweeps
     const bool chunks = resident_sweeps(c, restricted_mode(c)) && !p.replica_exchange;
+    const bool pipe = pipelined_sweeps(c, restricted_mode(c));
     for (int it = 0; it < iters; ++it) {
         for (int j = 0; chunks && j < nsw; j += kChainSweeps) {
             ChainArgs a = chain_args(c, restricted_mode(c), std::min(kChainSweeps, nsw - j));
@@ -845,7 +949,12 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
             enqueue_chain<T>(c, a);
             if ((j / kChainSweeps & 15) == 15) HIPCHK(hipStreamSynchronize(c->stream));   // bound the queue depth
         }
-        for (int j = 0; !chunks && j < nsw; ++j) {
+        if (pipe) {
+            st = enqueue_pipelined<T>(c, restricted_mode(c),
+                                      {nsw, 0, K, nsw - 1, p.n_th, p.replica_exchange != 0, nullptr, nullptr});
+            if (st != LLR_OK) return st;
+        }
+        for (int j = 0; !chunks && !pipe && j < nsw; ++j) {
             const bool rec = ((j + 1) % K == 0) || (j == nsw - 1);
             st = launch_sweep<T>(c, rec, p.replica_exchange != 0, j >= p.n_th);
             if (st != LLR_OK) return st;
@@ -905,9 +1014,14 @@ static llr_status plain_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, int m
         if (bits) dB = (uint16_t*)((char*)c->stage + (E_hist ? 8 * (size_t)rows * n : 0));
     }
     const bool chunks = resident_sweeps(c, mode) && mode != LLR_MODE_APPROACH;
+    const bool pipe = pipelined_sweeps(c, mode);
     for (int t0 = 0; t0 < n_sweeps; t0 += rows) {
         const int m = std::min(rows, n_sweeps - t0);
-        for (int t = 0; t < m;) {
+        if (pipe) {
+            const llr_status st = enqueue_pipelined<T>(c, mode, {m, t0, K, -1, m, false, dE, dB});
+            if (st != LLR_OK) return st;
+        }
+        for (int t = 0; !pipe && t < m;) {
             double* eRow = dE ? dE + (size_t)t * n : nullptr;
             uint16_t* bRow = dB ? dB + (size_t)t * n : nullptr;
             if (chunks) {
@@ -1037,6 +1151,7 @@ void llr_destroy(llr_ctx* c) {
     }
     if (c->fork_ev) hipEventDestroy(c->fork_ev);
     if (c->join_ev) hipEventDestroy(c->join_ev);
+    if (c->half_ev) hipEventDestroy(c->half_ev);
     for (auto& p : c->pending) { hipEventDestroy(p.a); hipEventDestroy(p.b); }
     for (auto e : c->pool) hipEventDestroy(e);
     for (void* p : c->allocs) hipFree(p);
@@ -1248,23 +1363,26 @@ llr_status llr_set_order(llr_ctx* c, int serpentine) {
 
 }  // extern "C"
 
-// The staggered order's second stream and its fork / join events.
-// All three are created or none is kept, so c->side set means all exist.
+// The second stream of the staggered order and of pipelined sweeps, and their
+// events.  All are created or none is kept, so c->side set means all exist.
 static llr_status ensure_side_stream(llr_ctx* c) {
     if (c->side) return LLR_OK;
     HIPCHK(hipSetDevice(c->device));
     hipStream_t st = nullptr;
-    hipEvent_t fe = nullptr, je = nullptr;
+    hipEvent_t fe = nullptr, je = nullptr, he = nullptr;
     hipError_t e = hipEventCreateWithFlags(&fe, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&je, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&he, hipEventDisableTiming);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
     if (e != hipSuccess) {
         if (fe) hipEventDestroy(fe);
         if (je) hipEventDestroy(je);
+        if (he) hipEventDestroy(he);
         return fail(LLR_EDEVICE, std::string("second stream: ") + hipGetErrorString(e));
     }
     c->fork_ev = fe;
     c->join_ev = je;
+    c->half_ev = he;
     c->side = st;
     return LLR_OK;
 }
