@@ -13,7 +13,7 @@
 // The arithmetic per link is that of the class-pass kernels (llr_link.hpp)
 // and the class sums are the same integers, so the results are theirs bit
 // for bit.  Measured per sweep (class passes before): L = 8 x 512 FP32 300 ->
-// 123 us, L = 8 x 32 FP32 ~130 -> 70 us, L = 4 x 8 FP64 133 -> 54 us.
+// 123 us, L = 8 x 32 FP32 ~130 -> 70 us, L = 4 x 8 FP64 133 -> 43 us.
 #include <hip/hip_runtime.h>
 
 #include "llr_internal.hpp"
@@ -116,15 +116,61 @@ __device__ __forceinline__ void chain_staples(const char* lat, int pb, int mu, i
     }
 }
 
-// Attempts 2, 3, ... of the links of one wavefront that rejected the first
-// two (about 9 %): the pending links are packed into slots and the 64 lanes
+// The value of lane J of each quad on all four of its lanes (one DPP move per word).
+template <int J>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x55 * J, 0xf, 0xf, false));
+}
+template <int J>
+__device__ __forceinline__ double quad_lane(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x55 * J, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x55 * J, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// The same with a link on the four lanes of a quad: lane j = 0..2 takes the two
+// staples of the j-th direction, lane 3 the sine and cosine of the link's own
+// angle t, and every lane gets all the results; the sums run in the same order.
+template <typename T>
+__device__ __forceinline__ void quad_staples(const char* lat, int pb, int mu, int p, const ChainLink& k, int q, T t,
+                                             T& C, T& S, T& so, T& co) {
+    using M = Math<T>;
+    const bool odd = ((k.s + p) & 1) != 0;
+    const int w0 = odd ? k.w0 & 0xffff : k.w0 & ~0xffff;
+    const int up_mu = lo16(mu == 0 ? w0 : (mu == 1 ? k.w[0] : (mu == 2 ? k.w[1] : k.w[2])));
+    const int mu_q = (2 * mu + (p ^ 1)) * pb;
+    const int j = q < 3 ? q : 2;
+    const int nu = j + (j >= mu ? 1 : 0);
+    const int wn = nu == 0 ? w0 : (nu == 1 ? k.w[0] : (nu == 2 ? k.w[1] : k.w[2]));
+    const int up_nu = lo16(wn), dn_nu = hi16(wn);
+    const int nu_p = (2 * nu + p) * pb, nu_q = (2 * nu + (p ^ 1)) * pb;
+    const T t_nu_pmu = lds_at<T>(lat, nu_q + k.hb + up_mu);
+    const T t_mu_pnu = lds_at<T>(lat, mu_q + k.hb + up_nu);
+    const T t_nu_x = lds_at<T>(lat, nu_p + k.hb);
+    const T t_nu_pmu_mnu = lds_at<T>(lat, nu_p + k.hb + up_mu + dn_nu);
+    const T t_mu_mnu = lds_at<T>(lat, mu_q + k.hb + dn_nu);
+    const T t_nu_mnu = lds_at<T>(lat, nu_q + k.hb + dn_nu);
+    const T sf = t_nu_pmu - t_mu_pnu - t_nu_x;
+    const T sb = t_nu_mnu - t_nu_pmu_mnu - t_mu_mnu;
+    T s1, c1, s2, c2;
+    M::sincos_rad(q == 3 ? t : sf, &s1, &c1);
+    M::sincos_rad(sb, &s2, &c2);
+    so = quad_lane<3>(s1);
+    co = quad_lane<3>(c1);
+    const T c = c1 + c2, z = s1 + s2;
+    C = quad_lane<0>(c) + quad_lane<1>(c) + quad_lane<2>(c);
+    S = quad_lane<0>(z) + quad_lane<1>(z) + quad_lane<2>(z);
+}
+
+// Attempts 2 m_from, ... of the links of one wavefront that rejected the ones
+// before (the first two: about 9 %): the pending links are packed into slots and the 64 lanes
 // are dealt out among them, G lanes per slot, lane i of a slot taking attempt
 // pair m0 + i; the first success in attempt order wins.  One round ends
 // nearly every wavefront's tail, with no block barrier.
 template <typename T, int LPT>
 __device__ __forceinline__ void chain_tail(bool (&got)[LPT], T (&ch)[LPT], T (&sh)[LPT], const T (&ak)[LPT],
-                                           const ChainLink (&k)[LPT], int* w_h, T* w_ak, uint32_t c1base,
-                                           uint32_t sweep, uint32_t c3, uint32_t k0, uint32_t k1) {
+                                           const ChainLink (&k)[LPT], int* w_h, T* w_ak, int m_from,
+                                           uint32_t c1base, uint32_t sweep, uint32_t c3, uint32_t k0, uint32_t k1) {
     const int lane = threadIdx.x & 63;
     bool open[LPT];
 #pragma unroll
@@ -141,7 +187,7 @@ __device__ __forceinline__ void chain_tail(bool (&got)[LPT], T (&ch)[LPT], T (&s
         }
         if (np == 0) return;
         np = min(np, 64);
-        for (int m0 = 1; np > 0 && m0 < kVmCap / 2;) {
+        for (int m0 = m_from; np > 0 && m0 < kVmCap / 2;) {
 #pragma unroll
             for (int r = 0; r < LPT; ++r)
                 if (mine[r] && !got[r]) {
@@ -193,7 +239,11 @@ __device__ __forceinline__ void chain_tail(bool (&got)[LPT], T (&ch)[LPT], T (&s
     }
 }
 
-// LPT links per thread, link e of thread tid at half index e NT + tid.
+// LPT links per thread, link e of thread tid at half index e NT + tid.  GRP = 4:
+// one link per quad of lanes.  A pass of L = 4 is one chain of dependent FP64
+// instructions (about 10 cycles each, one wavefront per SIMD), which the quad
+// shortens: a lane takes two of the six staples, and two of the link's first eight
+// sampler attempts, so that the tail below runs once in 10^4 links.
 // Decisions, counters, measurement and recompute are those of the last block
 // of a class pass, k_end_sweep and k_energy; every thread takes the class
 // decision itself from the block's partial sums, which saves a barrier.
@@ -203,16 +253,19 @@ __device__ __forceinline__ void chain_tail(bool (&got)[LPT], T (&ch)[LPT], T (&s
 // and the first wavefront walks them.  A launch of one pass waits for the chain
 // with most re-draws (L = 8 x 32 FP32: 60 us a pass, the chains' mean 15); here
 // each chain goes on to its next pass by itself (534 -> 203 us per sweep).
-template <typename T, int LPT, int MAXT, int VAR>
-__global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ th, DevState s, ChainArgs a) {
+template <typename T, int LPT, int MAXT, int VAR, int GRP>
+__global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T* __restrict__ th, DevState s, ChainArgs a) {
     using M = Math<T>;
     constexpr bool FUSED = VAR == kHbFuseOr;
+    static_assert(GRP == 1 || (GRP == 4 && LPT == 1 && VAR != kHbPre), "a quad of lanes holds one link");
     extern __shared__ __align__(16) char lat[];   // 8 planes of V/2 angles
     __shared__ long long part[2][MAXT / 64];
     __shared__ int w_h[MAXT / 64][64];
     __shared__ T w_ak[MAXT / 64][64];
     const int g = (int)blockIdx.x, tid = (int)threadIdx.x, NT = (int)blockDim.x;
     const int wid = tid >> 6, lane = tid & 63, nw = NT >> 6;
+    const int tl = tid / GRP, NL = NT / GRP;      // a thread's first link, and their stride
+    const bool lead = GRP == 1 || tid % GRP == 0;   // the lane that writes and counts a link
     int li = 0;
 #pragma unroll 1
     while (li + 1 < lt.n && g >= lt.l[li + 1].chain0) ++li;
@@ -232,7 +285,7 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
         }
         ChainLink k[LPT];
 #pragma unroll
-        for (int r = 0; r < LPT; ++r) k[r] = chain_link<T>(L, r * NT + tid);
+        for (int r = 0; r < LPT; ++r) k[r] = chain_link<T>(L, r * NL + tl);
         const int gi = s.itv[g];
         const double lo = s.lo[gi], hi = s.hi[gi];
         const double afix = a.mode == kModeMuca ? s.mu_b[li] : s.a[gi];
@@ -253,17 +306,21 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                 const int colour = ps & 7, mu = colour >> 1, p = colour & 1;
                 const bool heat = FUSED || (ps < 8) != b_half;
                 char* own = lat + colour * pb;
-                T C[LPT], S[LPT], t_old[LPT];
+                T C[LPT], S[LPT], t_old[LPT], so[LPT], co[LPT];
 #pragma unroll
                 for (int r = 0; r < LPT; ++r) {
-                    chain_staples<T>(lat, pb, mu, p, k[r], C[r], S[r]);
                     t_old[r] = lds_at<T>(own, k[r].hb);
+                    if constexpr (GRP == 4) quad_staples<T>(lat, pb, mu, p, k[r], tid & 3, t_old[r], C[r], S[r], so[r], co[r]);
+                    else chain_staples<T>(lat, pb, mu, p, k[r], C[r], S[r]);
                 }
                 if (!heat) {
 #pragma unroll
                     for (int r = 0; r < LPT; ++r) {
-                        const T tn = or_angle(t_old[r], C[r], S[r]);
-                        if ((r * NT + tid < V2)) *reinterpret_cast<T*>(own + k[r].hb) = tn;
+                        T tn;
+                        if constexpr (GRP == 4) tn = or_angle_sc(t_old[r], so[r], co[r], C[r], S[r]);
+                        else tn = or_angle(t_old[r], C[r], S[r]);
+                        // (all staples of the class are of other planes: no barrier before the write)
+                        if (lead && r * NL + tl < V2) *reinterpret_cast<T*>(own + k[r].hb) = tn;
                     }
                     __syncthreads();
                     continue;
@@ -274,26 +331,43 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                 bool got[LPT];
 #pragma unroll
                 for (int r = 0; r < LPT; ++r) {
-                    T so, co;
-                    M::sincos_rad(t_old[r], &so, &co);
-                    eps_old[r] = fms2(C[r], co, S[r], so);
+                    if constexpr (GRP == 1) M::sincos_rad(t_old[r], &so[r], &co[r]);
+                    eps_old[r] = fms2(C[r], co[r], S[r], so[r]);
                     // rejected class: the old angle, or its overrelaxation in the fused order
                     t_rej[r] = t_old[r];
-                    if constexpr (FUSED) t_rej[r] = or_angle_sc(t_old[r], so, co, C[r], S[r]);
+                    if constexpr (FUSED) t_rej[r] = or_angle_sc(t_old[r], so[r], co[r], C[r], S[r]);
                     R[r] = M::sqrt_(fma2(C[r], C[r], S[r], S[r]));
                     kap[r] = (T)acoup * R[r];
                     ak[r] = kap[r] < T(0) ? -kap[r] : kap[r];
                     ch[r] = T(1);
                     sh[r] = T(0);
                     got[r] = true;
-                    if ((r * NT + tid < V2)) {
+                    if ((r * NL + tl < V2)) {
                         T q, rm1, kg2;
                         vm_constants(ak[r], q, rm1, kg2);
-                        const uint4 w = philox10(make_uint4((uint32_t)(r * NT + tid), c1base, sweep, c3), a.k0, a.k1);
-                        got[r] = vm_first_two(w, ak[r], q, rm1, kg2, ch[r], sh[r]);
+                        if constexpr (GRP == 4) {   // two of the first eight attempts per lane
+                            const uint4 w = philox10(make_uint4((uint32_t)(r * NL + tl), c1base | (uint32_t)(tid & 3), sweep,
+                                                                c3), a.k0, a.k1);
+                            got[r] = vm_first_two(w, ak[r], q, rm1, kg2, ch[r], sh[r]);
+                        } else {
+                            const uint4 w = philox10(make_uint4((uint32_t)(r * NL + tl), c1base, sweep, c3), a.k0, a.k1);
+                            got[r] = vm_first_two(w, ak[r], q, rm1, kg2, ch[r], sh[r]);
+                        }
                     }
                 }
-                chain_tail<T, LPT>(got, ch, sh, ak, k, w_h[wid], w_ak[wid], c1base, sweep, c3, a.k0, a.k1);
+                if constexpr (GRP == 4) {
+                    // the first lane of the quad that accepted
+                    const unsigned m = (unsigned)(__ballot(got[0]) >> (lane & ~3)) & 15u;
+                    const int src = (lane & ~3) + (m ? __ffs((int)m) - 1 : 0);
+                    ch[0] = lane_read(ch[0], src);
+                    sh[0] = lane_read(sh[0], src);
+                    const bool none = m == 0;
+                    got[0] = !(none && lead);   // only the leading lane's values count from here on
+                    if (any_lane(none))
+                        chain_tail<T, LPT>(got, ch, sh, ak, k, w_h[wid], w_ak[wid], 4, c1base, sweep, c3, a.k0, a.k1);
+                } else {
+                    chain_tail<T, LPT>(got, ch, sh, ak, k, w_h[wid], w_ak[wid], 1, c1base, sweep, c3, a.k0, a.k1);
+                }
                 if constexpr (VAR == kHbPre) {
                     long long* sd = reinterpret_cast<long long*>(lat + 8 * pb);
                     T* sc = reinterpret_cast<T*>(sd + V2);
@@ -302,7 +376,7 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                     for (int r = 0; r < LPT; ++r) {
                         T tn = t_old[r], dE = T(0);
                         if (got[r]) hb_new_angle(ch[r], sh[r], C[r], S[r], R[r], kap[r], eps_old[r], tn, dE);
-                        const int h = r * NT + tid;
+                        const int h = r * NL + tl;
                         if (h < V2) {
                             sd[h] = got[r] ? link_fixed(dE, L) : kLinkNone;
                             sc[h] = C[r];
@@ -334,7 +408,7 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                 for (int r = 0; r < LPT; ++r) {
                     T dE = T(0);
                     t_new[r] = t_rej[r];
-                    if ((r * NT + tid < V2) && got[r]) {
+                    if (lead && r * NL + tl < V2 && got[r]) {
                         if constexpr (FUSED) hb_or_new_angle(ch[r], sh[r], C[r], S[r], R[r], kap[r], eps_old[r], t_new[r], dE);
                         else hb_new_angle(ch[r], sh[r], C[r], S[r], R[r], kap[r], eps_old[r], t_new[r], dE);
                     }
@@ -385,7 +459,7 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
                 if (acc || FUSED) {
 #pragma unroll
                     for (int r = 0; r < LPT; ++r)
-                        if ((r * NT + tid < V2)) *reinterpret_cast<T*>(own + k[r].hb) = acc ? t_new[r] : t_rej[r];
+                        if (lead && r * NL + tl < V2) *reinterpret_cast<T*>(own + k[r].hb) = acc ? t_new[r] : t_rej[r];
                 }
                 __syncthreads();
             }
@@ -490,6 +564,14 @@ __global__ __launch_bounds__(MAXT, 4) void k_chain(LatTable lt, T* __restrict__ 
 // 1024 / 512 threads: 32 chains 70.3 / 78.7, 256 chains 71.2 / 80.0, 300
 // chains 140.5 / 121.3, 512 chains 141.1 / 123.2.
 constexpr size_t kChainLds = 131072;
+// Four lanes per link while the 4 x 128 links of L = 4 leave a CU's SIMDs two
+// wavefronts each and every chain has a CU of its own; beyond that the work the
+// lanes of a quad repeat (constants, new angle) costs more than the shorter chain
+// of dependent instructions saves.  Measured, us per sweep one lane / four, L = 4:
+// FP64 8 chains 49.2 / 42.8, 256 chains 48.4 / 43.1, 300 chains 70.9 / over 90;
+// FP32 8 chains 20.4 / 18.7, 256 chains 20.5 / 19.0, 300 chains 24.8 / 29.
+constexpr uint32_t kQuadLinks = 128;
+constexpr int kQuadChains = 256;
 
 static size_t chain_lds(uint32_t v2, size_t elem, bool per_link) {
     return v2 * (8 * elem + (per_link ? 8 + 3 * elem : 0));
@@ -503,9 +585,9 @@ bool chain_fits(const LatTable& lt, size_t elem, bool per_link) {
     return lt.n > 0;
 }
 
-template <typename T, int LPT, int MAXT, int VAR>
+template <typename T, int LPT, int MAXT, int VAR, int GRP = 1>
 static hipError_t allow_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chain<T, LPT, MAXT, VAR>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chain<T, LPT, MAXT, VAR, GRP>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainLds);
 }
 template <typename T, int LPT, int MAXT>
@@ -527,15 +609,15 @@ hipError_t chain_setup() {
     return e;
 }
 
-template <typename T, int LPT, int MAXT, int VAR>
+template <typename T, int LPT, int MAXT, int VAR, int GRP = 1>
 static void launch_var(const LatTable& lt, T* th, DevState s, const ChainArgs& a, uint32_t v2, hipStream_t st) {
-    const dim3 gr(lt.n_chains), bl(((v2 + LPT - 1) / LPT + 63) / 64 * 64);
-    hipLaunchKernelGGL((k_chain<T, LPT, MAXT, VAR>), gr, bl, chain_lds(v2, sizeof(T), VAR == kHbPre), st, lt, th, s, a);
+    const dim3 gr(lt.n_chains), bl(((v2 + LPT - 1) / LPT * GRP + 63) / 64 * 64);
+    hipLaunchKernelGGL((k_chain<T, LPT, MAXT, VAR, GRP>), gr, bl, chain_lds(v2, sizeof(T), VAR == kHbPre), st, lt, th, s, a);
 }
-template <typename T, int LPT, int MAXT>
+template <typename T, int LPT, int MAXT, int GRP = 1>
 static void launch_shape(const LatTable& lt, T* th, DevState s, const ChainArgs& a, uint32_t v2, hipStream_t st) {
-    if (a.order == 1) launch_var<T, LPT, MAXT, kHbFuseOr>(lt, th, s, a, v2, st);
-    else launch_var<T, LPT, MAXT, kHbPlain>(lt, th, s, a, v2, st);
+    if (a.order == 1) launch_var<T, LPT, MAXT, kHbFuseOr, GRP>(lt, th, s, a, v2, st);
+    else launch_var<T, LPT, MAXT, kHbPlain, GRP>(lt, th, s, a, v2, st);
 }
 
 template <typename T>
@@ -545,6 +627,10 @@ void launch_chain(const LatTable& lt, T* th, DevState s, const ChainArgs& a, hip
     if (a.mode == kModeLink) {
         if (v2 <= 1024) launch_var<T, 1, 1024, kHbPre>(lt, th, s, a, v2, st);
         else if constexpr (sizeof(T) == 4) launch_var<T, 2, 1024, kHbPre>(lt, th, s, a, v2, st);
+        return;
+    }
+    if (v2 <= kQuadLinks && lt.n_chains <= kQuadChains) {
+        launch_shape<T, 1, 512, 4>(lt, th, s, a, v2, st);
         return;
     }
     if (v2 <= 1024) {

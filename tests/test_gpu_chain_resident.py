@@ -43,6 +43,10 @@ def _state(ctx, n_lat):
 CASES = [  # lattices (L, chains): one link to several per thread, idle lanes, mixed sizes, more chains than CUs
     ([(4, 1)], "f64", "grouped", False),
     ([(4, 5)], "f32", "staggered", True),
+    ([(4, 7)], "f64", "interleaved", True),     # four lanes per link
+    ([(2, 3), (4, 4)], "f32", "interleaved", False),
+    ([(4, 257)], "f32", "grouped", True),
+    ([(4, 513)], "f64", "grouped", False),
     ([(6, 3)], "f64", "interleaved", True),
     ([(6, 5), (4, 3)], "f32", "grouped", False),
     ([(8, 3)], "f32", "interleaved", False),
