@@ -288,33 +288,27 @@ static void set_tiles(LatTable& lt, int hb_lpt, int or_lpt) {
     lt.or_blocks = or0;
 }
 
-// The staggered order's two chain sets: per lattice, the first ceil(n/2)
-// chains (A) and the others (B), as tables of their own (a lattice may hold
-// no chain in B; its block ranges are then empty).
-static void half_tables(const LatTable& lt, LatTable& a, LatTable& b) {
-    a = lt;
-    b = lt;
-    a.n_chains = b.n_chains = 0;
-    for (int i = 0; i < lt.n; ++i) {
-        const LatDev& d = lt.l[i];
-        const int na = (d.n_chains + 1) / 2;
-        a.l[i].n_chains = na;
-        b.l[i].n_chains = d.n_chains - na;
-        b.l[i].chain0 = d.chain0 + na;
-        b.l[i].base = d.base + (long long)na * 16ll * (long long)d.V2;
-        b.l[i].lbase = d.lbase + (long long)na * (long long)d.V2;
-        a.n_chains += na;
-        b.n_chains += d.n_chains - na;
+// Part i of n of every lattice's chains, as a table of its own (a lattice may
+// hold no chain in a part; its block ranges are then empty).  Part 0 of 2 has the
+// first ceil(n/2) chains of each lattice: the staggered order's first chain set.
+static LatTable chain_part(const LatTable& lt, int i, int n) {
+    LatTable t = lt;
+    t.n_chains = 0;
+    t.site_blocks = 0;
+    for (int k = 0; k < lt.n; ++k) {
+        const LatDev& d = lt.l[k];
+        const int c0 = (int)(((long long)d.n_chains * i + n - 1) / n);
+        const int c1 = (int)(((long long)d.n_chains * (i + 1) + n - 1) / n);
+        t.l[k].n_chains = c1 - c0;
+        t.l[k].chain0 = d.chain0 + c0;
+        t.l[k].base = d.base + (long long)c0 * 16ll * (long long)d.V2;
+        t.l[k].lbase = d.lbase + (long long)c0 * (long long)d.V2;
+        t.n_chains += c1 - c0;
+        t.l[k].eblock0 = t.site_blocks;   // site kernels on a part
+        t.site_blocks += (c1 - c0) * d.ebpc;
     }
-    set_tiles(a, lt.hb_lpt, lt.or_lpt);
-    set_tiles(b, lt.hb_lpt, lt.or_lpt);
-    for (LatTable* t : {&a, &b}) {   // site kernels on the halves
-        t->site_blocks = 0;
-        for (int i = 0; i < t->n; ++i) {
-            t->l[i].eblock0 = t->site_blocks;
-            t->site_blocks += t->l[i].n_chains * t->l[i].ebpc;
-        }
-    }
+    set_tiles(t, lt.hb_lpt, lt.or_lpt);
+    return t;
 }
 
 static llr_status layout(llr_ctx* c) {
@@ -560,8 +554,7 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
         a.every = recompute ? 1 : 0;
         a.end_sweep = 0;
         enqueue_chain<T>(c, a);
-        if (replica) launch_replica(c->lt, c->ds, a.k0, a.k1, c->stream);
-        launch_end_sweep(c->lt, c->ds, measure ? 1 : 0, 0, 1, E_row, b_row, c->stream);
+        launch_end_sweep(c->lt, c->ds, replica ? 1 : 0, measure ? 1 : 0, 0, 1, a.k0, a.k1, E_row, b_row, c->stream);
         return;
     }
     const bool plain = plain_mode(mode);
@@ -577,8 +570,7 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
         // overrelaxation of 0..7; chains of B on the side stream:
         // overrelaxation first.  The two sets share no link, so the streams
         // join only at the end of the sweep.
-        LatTable ha, hb;
-        half_tables(c->lt, ha, hb);
+        const LatTable ha = chain_part(c->lt, 0, 2), hb = chain_part(c->lt, 1, 2);
         const uint32_t k0 = (uint32_t)c->prm.seed, k1 = (uint32_t)(c->prm.seed >> 32);
         TimeScope ts(c, 0, 16);
         hipEventRecord(c->fork_ev, c->stream);
@@ -604,8 +596,8 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
         }
     }
     if (recompute) enqueue_energy<T>(c, recompute_check(mode));
-    if (replica) launch_replica(c->lt, c->ds, (uint32_t)c->prm.seed, (uint32_t)(c->prm.seed >> 32), c->stream);
-    launch_end_sweep(c->lt, c->ds, measure ? 1 : 0, 0, 1, E_row, b_row, c->stream);
+    launch_end_sweep(c->lt, c->ds, replica ? 1 : 0, measure ? 1 : 0, 0, 1, (uint32_t)c->prm.seed,
+                     (uint32_t)(c->prm.seed >> 32), E_row, b_row, c->stream);
 }
 
 static llr_status ensure_link_buffers(llr_ctx* c);
@@ -640,6 +632,28 @@ static bool pipelined_sweeps(const llr_ctx* c, int mode) {
     return two && links * (c->precision == LLR_FP32 ? 1 : 2) >= kPipeLinks;
 }
 
+// The parts of a half that go through their sweep one after another, each its
+// heatbath and at once its overrelaxation: a half whose angles (both planes) outgrow
+// the 256 MB last-level cache would read them from HBM again in every pass.  Us per
+// sweep with the halves whole / in parts of at most 240 MB, FP32: L = 20 x 192 (492 MB
+// a half) 1893 / 1620, 20 x 128 (328 MB) 1202 / 1078, 16 x 256 (268 MB) 916 / 874,
+// 20 x 96 (246 MB) 848 / 822; FP64 20 x 64 (328 MB) 2064 / 1964.  Below it a part is
+// only a smaller launch: 18 x 128 staggered (215 MB) 784 / 856, 18 x 96 (161 MB)
+// 568 / 633 in two parts.
+constexpr size_t kPartBytes = 240000000;
+
+static std::vector<LatTable> pipe_parts(const llr_ctx* c, const LatTable& half) {
+    size_t bytes = 0;
+    for (int i = 0; i < half.n; ++i) bytes += (size_t)half.l[i].n_chains * 16 * half.l[i].V2 * elem_size(c);
+    const int np = (int)((bytes + kPartBytes - 1) / kPartBytes);
+    std::vector<LatTable> out;
+    for (int i = 0; i < np; ++i) {
+        const LatTable t = chain_part(half, i, np);
+        if (t.n_chains > 0) out.push_back(t);
+    }
+    return out;
+}
+
 // A run of sweeps: recompute E after sweep j0 + t where every divides its index
 // + 1 and after `last`; accumulate E from sweep t = measure_from on.
 struct SweepRun {
@@ -654,8 +668,8 @@ template <typename T>
 static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
     llr_status st = ensure_side_stream(c);
     if (st != LLR_OK) return st;
-    LatTable ha, hb;
-    half_tables(c->lt, ha, hb);
+    const LatTable ha = chain_part(c->lt, 0, 2), hb = chain_part(c->lt, 1, 2);
+    const std::vector<LatTable> pa = pipe_parts(c, ha), pb = pipe_parts(c, hb);
     const uint32_t k0 = (uint32_t)c->prm.seed, k1 = (uint32_t)(c->prm.seed >> 32);
     T* th = (T*)c->state;
     const int check = recompute_check(mode), n = c->lt.n_chains;
@@ -668,36 +682,39 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
     const bool relax_first = c->stagger;   // the second half's sweep starts with its overrelaxation
     for (int t = 0; t < r.n; ++t) {
         const bool rec = r.recompute(t);
-        if (!relax_first) heat(ha, c->stream);
+        if (!relax_first) heat(pa[0], c->stream);
         if (t == 0) {   // grouped: the second half starts half a sweep later
             HIPCHK(hipEventRecord(c->fork_ev, c->stream));
             HIPCHK(hipStreamWaitEvent(c->side, c->fork_ev, 0));
         }
         if (relax_first) {
-            relax(hb, c->side);
-            heat(ha, c->stream);
+            relax(pb[0], c->side);
+            heat(pa[0], c->stream);
+        }
+        for (size_t i = 1; i < pa.size(); ++i) {
+            relax(pa[i - 1], c->stream);
+            heat(pa[i], c->stream);
+        }
+        relax(pa.back(), c->stream);
+        if (rec) launch_energy<T>(ha, th, c->ds, c->stream, false, check);
+        if (t > 0) HIPCHK(hipStreamWaitEvent(c->side, c->join_ev, 0));   // the labels and counters of sweep t
+        for (size_t i = 0; i < pb.size(); ++i) {
+            if (i > 0) relax(pb[relax_first ? i : i - 1], c->side);
+            heat(pb[i], c->side);
         }
         if (rec) {
-            relax(ha, c->stream);
-            launch_energy<T>(ha, th, c->ds, c->stream, false, check);
-        }
-        HIPCHK(hipEventRecord(c->half_ev, c->stream));   // E of the first half is final for this sweep
-        if (!rec) relax(ha, c->stream);
-        heat(hb, c->side);
-        if (rec) {
-            if (!relax_first) relax(hb, c->side);
+            if (!relax_first) relax(pb.back(), c->side);
             launch_energy<T>(hb, th, c->ds, c->side, false, check);
         }
-        HIPCHK(hipStreamWaitEvent(c->side, c->half_ev, 0));
-        if (r.replica) launch_replica(c->lt, c->ds, k0, k1, c->side);
-        launch_end_sweep(c->lt, c->ds, t >= r.measure_from ? 1 : 0, 0, 1, r.E_hist ? r.E_hist + (size_t)t * n : nullptr,
-                         r.bits_hist ? r.bits_hist + (size_t)t * n : nullptr, c->side);
-        HIPCHK(hipEventRecord(c->join_ev, c->side));
-        if (!rec && !relax_first) relax(hb, c->side);
-        // the first half's next sweep needs the labels and counters, not the second half's overrelaxation
-        HIPCHK(hipStreamWaitEvent(c->stream, c->join_ev, 0));
+        HIPCHK(hipEventRecord(c->half_ev, c->side));   // E of the second half is final for this sweep
+        if (!rec && !relax_first) relax(pb.back(), c->side);
+        HIPCHK(hipStreamWaitEvent(c->stream, c->half_ev, 0));
+        launch_end_sweep(c->lt, c->ds, r.replica ? 1 : 0, t >= r.measure_from ? 1 : 0, 0, 1, k0, k1,
+                         r.E_hist ? r.E_hist + (size_t)t * n : nullptr,
+                         r.bits_hist ? r.bits_hist + (size_t)t * n : nullptr, c->stream);
+        HIPCHK(hipEventRecord(c->join_ev, c->stream));
         note_sweep(c, false);
-        if ((t & 127) == 127) HIPCHK(hipStreamSynchronize(c->side));   // bound the queue depth
+        if ((t & 127) == 127) HIPCHK(hipStreamSynchronize(c->stream));   // bound the queue depth
     }
     HIPCHK(hipEventRecord(c->join_ev, c->side));
     HIPCHK(hipStreamWaitEvent(c->stream, c->join_ev, 0));
@@ -753,7 +770,7 @@ static llr_status launch_sweep(llr_ctx* c, bool recompute, bool replica, bool me
 template <typename T>
 static void enqueue_approach_sweep(llr_ctx* c) {
     for (int col = 0; col < 8; ++col) enqueue_hb_pass<T>(c, col, LLR_MODE_APPROACH, kApproach);
-    launch_end_sweep(c->lt, c->ds, 0, 1, 0, nullptr, nullptr, c->stream);
+    launch_end_sweep(c->lt, c->ds, 0, 0, 1, 0, 0, 0, nullptr, nullptr, c->stream);
 }
 
 template <typename T>

@@ -150,12 +150,12 @@ template <typename T> void launch_energy(const LatTable& lt, const T* th, DevSta
                                           bool with_obs = false, int check = 0);
 template <typename T> void launch_export(const LatTable& lt, int li, const T* th, DevState s, T* out, hipStream_t st);
 template <typename T> void launch_import(const LatTable& lt, int li, T* th, DevState s, const T* in, hipStream_t st);
-// E_row, b_row (optional, one entry per chain): the sweep's E and accept bits
-void launch_end_sweep(const LatTable& lt, DevState s, int measure, int approach, int with_or, double* E_row,
-                      uint16_t* b_row, hipStream_t st);
+// replica: the exchange at this sweep comes first; E_row, b_row (optional, one
+// entry per chain): the sweep's E and accept bits
+void launch_end_sweep(const LatTable& lt, DevState s, int replica, int measure, int approach, int with_or,
+                      uint32_t k0, uint32_t k1, double* E_row, uint16_t* b_row, hipStream_t st);
 // E and the adjoint plaquette sum of the chain serving each interval
 void launch_obs_row(const LatTable& lt, DevState s, double* E_row, double* B_row, hipStream_t st);
-void launch_replica(const LatTable& lt, DevState s, uint32_t k0, uint32_t k1, hipStream_t st);
 void launch_rm_update(const LatTable& lt, DevState s, RunCfg cfg, hipStream_t st);
 void launch_approach_init(const LatTable& lt, DevState s, hipStream_t st);
 void launch_approach_check(const LatTable& lt, DevState s, hipStream_t st);

@@ -880,32 +880,6 @@ __global__ __launch_bounds__(kBlock) void k_import(LatDev L, T* __restrict__ th,
     }
 }
 
-// ---------------------------------------------------------------------------
-// Per-sweep bookkeeping (one block): accumulate the measured energy of every
-// interval, move the accept bits to the log, advance the sweep counter.
-// ---------------------------------------------------------------------------
-// Overrelaxation passes are always accepted (E unchanged): their bits 8..15
-// are set here for sweeps that ran them.
-__global__ __launch_bounds__(1024) void k_end_sweep(int n, DevState s, int measure, int approach, int with_or,
-                                                    double* __restrict__ E_row, uint16_t* __restrict__ b_row) {
-    const long long row = s.bits_row ? *s.bits_row : 0;
-    for (int g = threadIdx.x; g < n; g += blockDim.x) {
-        if (measure) s.sumE[s.itv[g]] += s.E[g];
-        const uint16_t bits = (uint16_t)(s.bits[g] | (with_or ? 0xff00u : 0u));
-        if (s.bits_log && row < s.bits_rows_max) s.bits_log[row * n + g] = bits;
-        s.bits_last[g] = bits;
-        s.bits[g] = 0;
-        if (E_row) E_row[g] = s.E[g];
-        if (b_row) b_row[g] = bits;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (approach) *s.approach_ctr += 1u;
-        else *s.sweep_ctr += 1u;
-        if (s.bits_row) *s.bits_row = row + 1;
-    }
-}
-
 __global__ __launch_bounds__(1024) void k_obs_row(int n, DevState s, double* __restrict__ E_row,
                                                   double* __restrict__ B_row) {
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
@@ -915,12 +889,17 @@ __global__ __launch_bounds__(1024) void k_obs_row(int n, DevState s, double* __r
     }
 }
 
+// ---------------------------------------------------------------------------
+// End of a sweep, one block: replica exchange, the measured energy of every
+// interval, the accept bits to the log, the sweep counter.  A chain of dependent
+// loads on a few KB, 6.5 us of which most is the launch: one kernel for what two
+// took 10 us for.
+// ---------------------------------------------------------------------------
 // Replica exchange (Sec. 2.5) between intervals k and k+1 of one lattice, for
 // k = t (mod 2) at sweep t; eligible iff each configuration lies in the other
 // interval; accepted with min(1, exp[(a_k - a_{k+1})(E_{k+1} - E_k)]).  Only
 // the chain <-> interval labels move.
-__global__ __launch_bounds__(1024) void k_replica(LatTable lt, DevState s, uint32_t k0, uint32_t k1) {
-    const uint32_t t = *s.sweep_ctr;
+__device__ __forceinline__ void replica_pairs(const LatTable& lt, const DevState& s, uint32_t t, uint32_t k0, uint32_t k1) {
     unsigned long long prop = 0, accd = 0;
     for (int li = 0; li < lt.n; ++li) {
         const LatDev& L = lt.l[li];
@@ -947,6 +926,33 @@ __global__ __launch_bounds__(1024) void k_replica(LatTable lt, DevState s, uint3
     }
     if (prop) atomicAdd(s.re_cnt, prop);
     if (accd) atomicAdd(s.re_cnt + 1, accd);
+}
+
+// Overrelaxation passes are always accepted (E unchanged): their bits 8..15
+// are set here for sweeps that ran them.
+__global__ __launch_bounds__(1024) void k_end_sweep(LatTable lt, DevState s, int replica, int measure, int approach,
+                                                    int with_or, uint32_t k0, uint32_t k1, double* __restrict__ E_row,
+                                                    uint16_t* __restrict__ b_row) {
+    const int n = lt.n_chains;
+    const long long row = s.bits_row ? *s.bits_row : 0;
+    const uint32_t t = approach ? *s.approach_ctr : *s.sweep_ctr;
+    for (int g = threadIdx.x; g < n; g += blockDim.x) {
+        const uint16_t bits = (uint16_t)(s.bits[g] | (with_or ? 0xff00u : 0u));
+        if (s.bits_log && row < s.bits_rows_max) s.bits_log[row * n + g] = bits;
+        s.bits_last[g] = bits;
+        s.bits[g] = 0;
+        if (E_row) E_row[g] = s.E[g];
+        if (b_row) b_row[g] = bits;
+    }
+    if (replica) replica_pairs(lt, s, t, k0, k1);
+    __syncthreads();   // every label is final, every thread has read the counters
+    if (measure)
+        for (int g = threadIdx.x; g < n; g += blockDim.x) s.sumE[s.itv[g]] += s.E[g];
+    if (threadIdx.x == 0) {
+        if (approach) *s.approach_ctr = t + 1u;
+        else *s.sweep_ctr = t + 1u;
+        if (s.bits_row) *s.bits_row = row + 1;
+    }
 }
 
 // Robbins-Monro step of every interval (eq. (kk21), Algorithm 1 sign):
@@ -1123,16 +1129,13 @@ void launch_import(const LatTable& lt, int li, T* th, DevState s, const T* in, h
     hipLaunchKernelGGL(k_import<T>, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, L, th, s, in);
 }
 
-void launch_end_sweep(const LatTable& lt, DevState s, int measure, int approach, int with_or, double* E_row,
-                      uint16_t* b_row, hipStream_t st) {
-    hipLaunchKernelGGL(k_end_sweep, dim3(1), dim3(1024), 0, st, lt.n_chains, s, measure, approach, with_or, E_row,
+void launch_end_sweep(const LatTable& lt, DevState s, int replica, int measure, int approach, int with_or,
+                      uint32_t k0, uint32_t k1, double* E_row, uint16_t* b_row, hipStream_t st) {
+    hipLaunchKernelGGL(k_end_sweep, dim3(1), dim3(1024), 0, st, lt, s, replica, measure, approach, with_or, k0, k1, E_row,
                        b_row);
 }
 void launch_obs_row(const LatTable& lt, DevState s, double* E_row, double* B_row, hipStream_t st) {
     hipLaunchKernelGGL(k_obs_row, dim3(1), dim3(1024), 0, st, lt.n_chains, s, E_row, B_row);
-}
-void launch_replica(const LatTable& lt, DevState s, uint32_t k0, uint32_t k1, hipStream_t st) {
-    hipLaunchKernelGGL(k_replica, dim3(1), dim3(1024), 0, st, lt, s, k0, k1);
 }
 void launch_rm_update(const LatTable& lt, DevState s, RunCfg cfg, hipStream_t st) {
     hipLaunchKernelGGL(k_rm_update, dim3(1), dim3(1024), 0, st, lt.n_chains, s, cfg);

@@ -3,7 +3,8 @@ staggered runs) against the class passes one after another, which the library
 runs while per-kernel timing is on.  The sequence of every chain is the same, so
 every result is equal bit for bit: no tolerance.  The sizes lie just above the
 rule's 900 000 class links (FP64 ones count twice), with odd numbers of chains,
-a lattice of a single chain, and recomputes inside and at the end of the run."""
+a lattice of a single chain, and recomputes inside and at the end of the run;
+the last two have halves just above the 240 MB from which they run in parts."""
 import numpy as np
 import pytest
 
@@ -22,6 +23,8 @@ CASES = [
     ([(14, 17), (16, 1), (12, 53)], "f32", "grouped", False),
     ([(14, 25)], "f64", "grouped", True),
     ([(10, 91)], "f64", "staggered", False),
+    ([(20, 93), (14, 3)], "f32", "grouped", True),
+    ([(20, 48)], "f64", "staggered", True),
 ]
 
 
