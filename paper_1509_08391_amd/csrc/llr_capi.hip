@@ -375,7 +375,7 @@ static llr_status layout(llr_ctx* c) {
     s.conv_sweeps = (long long*)(s.E + n);
     s.conv_iter = (int*)(s.conv_sweeps + n);
     s.conf = s.conv_iter + n;
-    AL(acc, n) AL(eacc, n) AL(oacc, n) AL(obs, n) AL(cur, 8 * n) AL(itv, n) AL(b, 8 * n) AL(eta, 8 * n)
+    AL(acc, kAccStride * n) AL(eacc, kAccStride * n) AL(oacc, kAccStride * n) AL(obs, n) AL(cur, 8 * n) AL(itv, n) AL(b, 8 * n) AL(eta, 8 * n)
     AL(sprev, 8 * n) AL(bits, n + 2) AL(bits_last, n + 2) AL(hb_prop, n) AL(hb_acc, n) AL(fu_acc, n) AL(health, n)
     AL(drift, n) AL(lo, n) AL(hi, n)
     AL(cen, n) AL(w, n) AL(sumE, n) AL(mu_lnrho, n)

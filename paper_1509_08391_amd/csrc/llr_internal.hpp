@@ -46,11 +46,19 @@ struct LatTable {
     int n_chains;          // total chains = total intervals
 };
 
+// 64-bit words between the chains' accumulators: one cache line each.  Every block
+// of a pass adds to its chain's, and additions to one line are carried out one after
+// another, about 10 ns each: packed, 16 chains shared a line, and a launch of some
+// hundred blocks ended with microseconds of nothing else (us per sweep packed / padded,
+// FP32: L = 12 x 16 117 / 103, 18 x 16 209 / 191, 20 x 10 228 / 192, 24 x 6 269 / 211;
+// L = 12 x 64 174 / 174).
+constexpr int kAccStride = 16;
+
 // Per-chain and per-interval device state (all indices global).
 struct DevState {
     // per chain
     double* E;             // current energy (incremental, FP64)
-    unsigned long long* acc;   // arrivals << 51 | fixed-point Delta E of the running pass
+    unsigned long long* acc;   // arrivals << 51 | fixed-point Delta E of the running pass, every kAccStride-th word
     unsigned long long* eacc;  // the same for the energy recompute
     unsigned long long* oacc;  // the same for the observable of the measurement recompute
     double* obs;           // adjoint plaquette sum, sum_P cos 2 theta_P (FP64, at the last measurement)

@@ -498,7 +498,7 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
     if constexpr (M::f32) tot = block_sum_i64(wave_sum_i32(fx32)) << (L.fxb - 25);
     else tot = block_sum_i64(wave_sum_i64(fx));
     long long total = 0;
-    if (threadIdx.x == 0 && chain_arrive(s.acc + g, tot, L.hb_bpc, &total)) {
+    if (threadIdx.x == 0 && chain_arrive(s.acc + (size_t)kAccStride * g, tot, L.hb_bpc, &total)) {
         const double E0 = s.E[g];
         const double En = E0 + (double)total * L.fxinv;
         const double lo = s.lo[gi], hi = s.hi[gi];
@@ -540,7 +540,7 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
                 if (mode != kModeTune) s.fu_acc[g] += 1ull;
             }
         }
-        atomicExch(s.acc + g, 0ull);
+        atomicExch(s.acc + (size_t)kAccStride * g, 0ull);
     }
 }
 
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(kBlock) void k_energy(LatTable lt, const T* __restr
     if (__syncthreads_or(bad) && threadIdx.x == 0) atomicOr(s.health + g, (uint32_t)kHealthNonFinite);
     const long long tot = block_sum_i64(wave_sum_i64(fx));
     long long total = 0;
-    if (threadIdx.x == 0 && chain_arrive(s.eacc + g, tot, L.ebpc, &total)) {
+    if (threadIdx.x == 0 && chain_arrive(s.eacc + (size_t)kAccStride * g, tot, L.ebpc, &total)) {
         const double En = (double)total * L.fxinv;
         if (check) {
             // health of the chain's incremental E: its drift from the
@@ -777,15 +777,15 @@ __global__ __launch_bounds__(kBlock) void k_energy(LatTable lt, const T* __restr
             if (f) atomicOr(s.health + g, f);
         }
         s.E[g] = En;
-        atomicExch(s.eacc + g, 0ull);
+        atomicExch(s.eacc + (size_t)kAccStride * g, 0ull);
     }
     if (OBS) {
         __syncthreads();   // block_sum_i64's shared partials are reused
         const long long ta = block_sum_i64(wave_sum_i64(fa));
         long long tb = 0;
-        if (threadIdx.x == 0 && chain_arrive(s.oacc + g, ta, L.ebpc, &tb)) {
+        if (threadIdx.x == 0 && chain_arrive(s.oacc + (size_t)kAccStride * g, ta, L.ebpc, &tb)) {
             s.obs[g] = (double)tb * L.fxinv;
-            atomicExch(s.oacc + g, 0ull);
+            atomicExch(s.oacc + (size_t)kAccStride * g, 0ull);
         }
     }
 }
