@@ -542,7 +542,7 @@ static void enqueue_chain(llr_ctx* c, const ChainArgs& a) {
 // sweeps of one chain-resident launch: bounds a launch's duration
 constexpr int kChainSweeps = 64;
 // class links from which sweeps run in two pipelined halves (pipelined_sweeps)
-constexpr long long kPipeLinks = 900000;
+constexpr long long kPipeLinks = 760000;
 
 // one restricted sweep of all chains, then recompute / replica exchange /
 // measurement; E_row, b_row: device rows for the sweep's E and accept bits
@@ -612,14 +612,15 @@ static llr_status ensure_side_stream(llr_ctx* c);
 // sweep later, with the sequence of every chain, and so every result, unchanged.
 // (Staggered sweeps have the half sweep between the halves already, and need no
 // more than this of a join.)  Half launches leave less work to hide their ramps
-// and are twice as many: below kPipeLinks class links (FP64 ones count twice) whole
-// launches from captured graphs are as fast or faster.  Measured, us per sweep
-// whole / halves, FP32: L = 20 x 128 1244 / 1175, 18 x 96 639 / 585, 16 x 64 333 /
-// 292, 12 x 96 (1.0 M links) 226 / 198, 14 x 48 (0.92 M) 214 / 208, 18 x 16 (0.84 M)
-// 210 / 239, 10 x 160 (0.8 M) 193 / 193, 12 x 64 (0.66 M) 177 / 190; FP64: 12 x 64
-// 408 / 360, 12 x 32 (0.33 M) 272 / 276, 14 x 16 (0.31 M) 270 / 278, 10 x 32 198 / 201.
-// (One captured graph per period of sweeps made the halves slower: 1198 us at
-// L = 20 x 128.)
+// and are twice as many: below kPipeLinks class links (FP64 ones count four times, as
+// their heatbath takes four times as long) whole launches from captured graphs are
+// as fast or faster.  Measured, us per sweep whole / halves, FP32: L = 20 x 128
+// 1251 / 1076, 20 x 64 614 / 538, 18 x 24 243 / 205, 18 x 16 (840 000 links) 191 / 174,
+// 12 x 80 (830 000) 204 / 174, 10 x 160 (800 000) 191 / 169, 14 x 40 (768 000)
+// 191 / 171, 12 x 64 (664 000) 174 / 178, 10 x 128 (640 000) 163 / 179; FP64: 12 x 64
+// 424 / 361, 12 x 24 (249 000) 248 / 221, 20 x 3 (240 000) 223 / 216, 14 x 8 (154 000)
+// 197 / 195.  (One captured graph per period of sweeps made the halves slower: 1198
+// instead of 1180 us at L = 20 x 128.)
 static bool pipelined_sweeps(const llr_ctx* c, int mode) {
     if (!plain_mode(mode) || c->interleave || c->timing || !c->use_graphs || resident_sweeps(c, mode))
         return false;
@@ -629,7 +630,7 @@ static bool pipelined_sweeps(const llr_ctx* c, int mode) {
         links += (long long)c->lt.l[i].n_chains * c->lt.l[i].V2;
         two = two || c->lt.l[i].n_chains > 1;
     }
-    return two && links * (c->precision == LLR_FP32 ? 1 : 2) >= kPipeLinks;
+    return two && links * (c->precision == LLR_FP32 ? 1 : 4) >= kPipeLinks;
 }
 
 // The parts of a half that go through their sweep one after another, each its
