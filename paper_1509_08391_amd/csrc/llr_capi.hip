@@ -603,26 +603,31 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
 static llr_status ensure_link_buffers(llr_ctx* c);
 static llr_status ensure_side_stream(llr_ctx* c);
 
-// Whether grouped (and staggered) sweeps of this mode run with the chains in two
-// halves on two streams.  The heatbath passes are bound by vector instructions and the
-// overrelaxation passes by memory, and a chain's overrelaxation passes neither
-// change its E nor depend on its interval label: the end of a sweep (replica
-// exchange, measurement, counters) only needs every chain's heatbath passes.  So
-// while one half runs its overrelaxation the other runs its heatbath, half a
-// sweep later, with the sequence of every chain, and so every result, unchanged.
-// (Staggered sweeps have the half sweep between the halves already, and need no
-// more than this of a join.)  Half launches leave less work to hide their ramps
-// and are twice as many: below kPipeLinks class links (FP64 ones count four times, as
-// their heatbath takes four times as long) whole launches from captured graphs are
-// as fast or faster.  Measured, us per sweep whole / halves, FP32: L = 20 x 128
-// 1251 / 1076, 20 x 64 614 / 538, 18 x 24 243 / 205, 18 x 16 (840 000 links) 191 / 174,
-// 12 x 80 (830 000) 204 / 174, 10 x 160 (800 000) 191 / 169, 14 x 40 (768 000)
-// 191 / 171, 12 x 64 (664 000) 174 / 178, 10 x 128 (640 000) 163 / 179; FP64: 12 x 64
-// 424 / 361, 12 x 24 (249 000) 248 / 221, 20 x 3 (240 000) 223 / 216, 14 x 8 (154 000)
-// 197 / 195.  (One captured graph per period of sweeps made the halves slower: 1198
+// Whether sweeps of this mode run with the chains in two halves on two streams.
+// Grouped order: the heatbath passes are bound by vector instructions and the
+// overrelaxation passes by memory, and a chain's overrelaxation passes neither change
+// its E nor depend on its interval label: the end of a sweep (replica exchange,
+// measurement, counters) only needs every chain's heatbath passes.  So while one half
+// runs its overrelaxation the other runs its heatbath, half a sweep later, with the
+// sequence of every chain, and so every result, unchanged.  The staggered order has
+// the half sweep between the halves already and needs no more than this of a join.
+// In the interleaved order the fused passes of one half fill the ramps and last waves
+// of the other's; the halves join at the end of each sweep.  Half launches leave less
+// work to hide their own ramps and are twice as many: below kPipeLinks class links
+// (FP64 ones count four times, as their heatbath takes four times as long) whole
+// launches from captured graphs are as fast or faster.  Measured, us per sweep whole /
+// halves, FP32: L = 20 x 128 1251 / 1076, 20 x 64 614 / 538, 18 x 24 243 / 205, 18 x
+// 16 (840 000 links) 191 / 174, 12 x 80 (830 000) 204 / 174, 10 x 160 (800 000) 191 /
+// 169, 14 x 40 (768 000) 191 / 171, 12 x 64 (664 000) 174 / 178, 10 x 128 (640 000)
+// 163 / 179; FP64: 12 x 64 424 / 361, 12 x 24 (249 000) 248 / 221, 20 x 3 (240 000)
+// 223 / 216, 14 x 8 (154 000) 197 / 195; interleaved, FP32: 20 x 128 839 / 770, 20 x
+// 64 444 / 385, 14 x 74 195 / 162, 14 x 48 150 / 135, 12 x 64 128 / 121, 10 x 128 118
+// / 122, 20 x 8 (640 000) 120 / 125; FP64: 12 x 64 332 / 273, 12 x 24 195 / 180, 14 x
+// 8 154 / 160.  Three or four sets on as many streams are slower than one (14 x 74:
+// 256, 260). (One captured graph per period of sweeps made the halves slower: 1198
 // instead of 1180 us at L = 20 x 128.)
 static bool pipelined_sweeps(const llr_ctx* c, int mode) {
-    if (!plain_mode(mode) || c->interleave || c->timing || !c->use_graphs || resident_sweeps(c, mode))
+    if (!plain_mode(mode) || c->timing || !c->use_graphs || resident_sweeps(c, mode))
         return false;
     long long links = 0;
     bool two = false;
@@ -675,12 +680,16 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
     T* th = (T*)c->state;
     const int check = recompute_check(mode), n = c->lt.n_chains;
     const auto heat = [&](const LatTable& t, hipStream_t s) {
-        for (int col = 0; col < 8; ++col) launch_hb_pass<T>(t, th, c->ds, col, mode, kSweep, k0, k1, s);
+        for (int col = 0; col < 8; ++col) {
+            if (c->interleave) launch_hb_or_pass<T>(t, th, c->ds, col, mode, k0, k1, s);
+            else launch_hb_pass<T>(t, th, c->ds, col, mode, kSweep, k0, k1, s);
+        }
     };
     const auto relax = [&](const LatTable& t, hipStream_t s) {
-        for (int col = 0; col < 8; ++col) launch_or_pass<T>(t, th, c->ds, col, 0, s);
+        for (int col = 0; col < 8 && !c->interleave; ++col) launch_or_pass<T>(t, th, c->ds, col, 0, s);
     };
-    const bool relax_first = c->stagger;   // the second half's sweep starts with its overrelaxation
+    // the halves start together; staggered: the second one's sweep with its overrelaxation
+    const bool relax_first = c->stagger || c->interleave;
     for (int t = 0; t < r.n; ++t) {
         const bool rec = r.recompute(t);
         if (!relax_first) heat(pa[0], c->stream);
@@ -714,7 +723,7 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
                          r.E_hist ? r.E_hist + (size_t)t * n : nullptr,
                          r.bits_hist ? r.bits_hist + (size_t)t * n : nullptr, c->stream);
         HIPCHK(hipEventRecord(c->join_ev, c->stream));
-        note_sweep(c, false);
+        note_sweep(c, c->interleave);
         if ((t & 127) == 127) HIPCHK(hipStreamSynchronize(c->stream));   // bound the queue depth
     }
     HIPCHK(hipEventRecord(c->join_ev, c->side));

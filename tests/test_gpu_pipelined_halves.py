@@ -1,10 +1,9 @@
-"""Sweeps with the chains in two halves on two streams (large grouped and
-staggered runs) against the class passes one after another, which the library
+"""Sweeps with the chains in two halves on two streams (large runs) against the class passes one after another, which the library
 runs while per-kernel timing is on.  The sequence of every chain is the same, so
 every result is equal bit for bit: no tolerance.  The sizes lie just above the
 rule's 760 000 class links (FP64 ones count four times), with odd numbers of chains,
 a lattice of a single chain, and recomputes inside and at the end of the run;
-the last two have halves just above the 240 MB from which they run in parts."""
+the last three have halves just above the 240 MB from which they run in parts."""
 import numpy as np
 import pytest
 
@@ -23,6 +22,9 @@ CASES = [
     ([(14, 17), (16, 1), (12, 39)], "f32", "grouped", False),
     ([(14, 11)], "f64", "grouped", True),
     ([(10, 39)], "f64", "staggered", False),
+    ([(14, 17), (16, 1), (12, 39)], "f32", "interleaved", True),
+    ([(14, 11)], "f64", "interleaved", False),
+    ([(20, 93), (14, 3)], "f32", "interleaved", True),
     ([(20, 93), (14, 3)], "f32", "grouped", True),
     ([(20, 48)], "f64", "staggered", True),
 ]
@@ -38,7 +40,8 @@ def test_halves_equal_the_class_passes(sizes, prec, order, replica):
         ctx = llr.Context(precision=llr.FP32 if prec == "f32" else llr.FP64, device=0)
         ctx.set_params(n_th=3, n_a=8, n_rm=2, seed=91, replica_exchange=replica, overlap=1.0, recompute_every=4,
                        approach_cap=4000)
-        ctx.set_sweep_order(llr.SWEEP_STAGGERED if order == "staggered" else llr.SWEEP_GROUPED)
+        ctx.set_sweep_order({"grouped": llr.SWEEP_GROUPED, "interleaved": llr.SWEEP_INTERLEAVED,
+                             "staggered": llr.SWEEP_STAGGERED}[order])
         for L, E_low, dE in lats:
             ctx.add_lattice(L, E_low, dE)
         ctx.bind_state()
