@@ -302,7 +302,13 @@ llr_status llr_set_tiles(llr_ctx *ctx, int hb_lpt, int or_lpt);
  * Results do not depend on it. */
 llr_status llr_set_order(llr_ctx *ctx, int serpentine);
 /* on != 0 (default): the sweeps of llr_run / llr_rm_step are captured once per
- * variant into HIP graphs and replayed (not while per-kernel timing is on). */
+ * variant into HIP graphs and replayed, and large runs go through their sweeps in
+ * two halves of the chains on two streams (the context's and a second one of
+ * default priority, joined before the call returns its results).  0, and while
+ * per-kernel timing is on: class pass after class pass.  Lattices that fit in LDS
+ * (L <= 8; with the restriction per link L <= 8 in FP32, L <= 6 in FP64) run any
+ * number of sweeps per launch either way, except while timing is on.  Results do
+ * not depend on any of it. */
 llr_status llr_set_graphs(llr_ctx *ctx, int on);
 /* One class pass of every chain: heatbath (heatbath != 0, acceptance by mode,
  * counters with sweep index sweep_index) or overrelaxation of colour c. */
@@ -356,7 +362,8 @@ llr_status llr_get_rates(llr_ctx *ctx, llr_rates *out);
  * drift seen.  clear != 0 resets both.  Every call that runs sweeps returns
  * LLR_ENUMERIC, after its work, while a flag is set. */
 llr_status llr_health(llr_ctx *ctx, uint32_t *flags, double *drift, int clear);
-/* Kernel timing with HIP events on the context stream: on/off, and the
+/* Kernel timing with HIP events on the context stream (the sweeps then run as
+ * class passes one after another): on/off, and the
  * summed duration (ms) and count of heatbath-pass, overrelaxation-pass and
  * energy launches since enabling.  The 8 heatbath (and the 8
  * overrelaxation) launches of a sweep share one event pair, so the average
