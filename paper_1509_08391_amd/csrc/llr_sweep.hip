@@ -546,7 +546,7 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
 
 // With 4 class links per thread the registers are kept to 72 (FP32, seven
 // wavefronts per SIMD) and 128 (FP64, four), which they fit without spills.
-// The FP32 pass is bound by vector-instruction issue: 314 per class link (332
+// The FP32 pass is bound by vector-instruction issue: 305 per class link (340
 // before the straight-line links and the buffer addressing), of which about 45
 // are a wavefront's prologue, queue and reduction shared by its 4 links.
 // Heatbath of L = 20 x 128 FP32: 97.2 -> 88.4 us (six wavefronts 92, eight 89.6,
