@@ -305,8 +305,8 @@ llr_status llr_set_order(llr_ctx *ctx, int serpentine);
  * variant into HIP graphs and replayed, and large runs go through their sweeps in
  * two halves of the chains on two streams (the context's and a second one of
  * default priority, joined before the call returns its results).  0, and while
- * per-kernel timing is on: class pass after class pass.  Lattices that fit in LDS
- * (L <= 8; with the restriction per link L <= 8 in FP32, L <= 6 in FP64) run any
+ * per-kernel timing is on: class pass after class pass.  Small lattices (L <= 8
+ * in FP32, L <= 6 in FP64), kept in LDS, run any
  * number of sweeps per launch either way, except while timing is on.  Results do
  * not depend on any of it. */
 llr_status llr_set_graphs(llr_ctx *ctx, int on);

@@ -555,8 +555,13 @@ __global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T
     }
 }
 
-// LDS of a chain and the launch shape.  A chain fits up to L = 8 (64 KB of
-// FP32 angles, 128 KB of FP64 ones, of a CU's 160 KB).  Threads per block: with
+// LDS of a chain and the launch shape.  FP32 chains run here up to L = 8 (64 KB of
+// a CU's 160 KB), FP64 ones up to L = 6: a chain has one CU, whose vector units the
+// 2048 links of L = 8 keep busy three times as long as in FP32, while class passes
+// spread few chains over all CUs (us per sweep here / class passes, L = 8 FP64 with
+// replica exchange: 3 chains 243 / 127, 128 chains 257 / 198, 256 chains 264 / 271,
+// 512 chains 511 / 432; L = 6 FP64: 3 chains 116 / 126, 256 chains 120 / 252; L = 8
+// FP32: 3 chains 85 / 86, 256 chains 91 / 150).  Threads per block: with
 // more chains than the 256 CUs an FP32 chain of L = 8 runs on 512 threads with
 // 4 links each, so that two blocks share a CU and one computes while the other
 // waits at a barrier; otherwise a chain gets up to 1024 threads, the shortest
@@ -564,6 +569,7 @@ __global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T
 // 1024 / 512 threads: 32 chains 70.3 / 78.7, 256 chains 71.2 / 80.0, 300
 // chains 140.5 / 121.3, 512 chains 141.1 / 123.2.
 constexpr size_t kChainLds = 131072;
+constexpr uint32_t kChainLinksF64 = 1024;
 // Four lanes per link while the 4 x 128 links of L = 4 leave a CU's SIMDs two
 // wavefronts each and every chain has a CU of its own; beyond that the work the
 // lanes of a quad repeat (constants, new angle) costs more than the shorter chain
@@ -578,10 +584,9 @@ static size_t chain_lds(uint32_t v2, size_t elem, bool per_link) {
 }
 
 // Whether every lattice's chain fits; per_link: with the candidates of a class
-// (L = 8 in FP32, L = 6 in FP64)
 bool chain_fits(const LatTable& lt, size_t elem, bool per_link) {
     for (int i = 0; i < lt.n; ++i)
-        if (chain_lds(lt.l[i].V2, elem, per_link) > kChainLds) return false;
+        if (chain_lds(lt.l[i].V2, elem, per_link) > kChainLds || (elem == 8 && lt.l[i].V2 > kChainLinksF64)) return false;
     return lt.n > 0;
 }
 
@@ -602,7 +607,6 @@ hipError_t chain_setup() {
     if (e == hipSuccess) e = shape_setup<float, 2, 1024>();
     if (e == hipSuccess) e = shape_setup<float, 4, 512>();
     if (e == hipSuccess) e = shape_setup<double, 1, 1024>();
-    if (e == hipSuccess) e = shape_setup<double, 2, 1024>();
     if (e == hipSuccess) e = allow_lds<float, 1, 1024, kHbPre>();
     if (e == hipSuccess) e = allow_lds<float, 2, 1024, kHbPre>();
     if (e == hipSuccess) e = allow_lds<double, 1, 1024, kHbPre>();
@@ -637,12 +641,10 @@ void launch_chain(const LatTable& lt, T* th, DevState s, const ChainArgs& a, hip
         launch_shape<T, 1, 1024>(lt, th, s, a, v2, st);
         return;
     }
-    if constexpr (sizeof(T) == 4)
-        if (lt.n_chains > 256) {
-            launch_shape<T, 4, 512>(lt, th, s, a, v2, st);
-            return;
-        }
-    launch_shape<T, 2, 1024>(lt, th, s, a, v2, st);
+    if constexpr (sizeof(T) == 4) {   // chain_fits: FP64 chains have at most 1024 links per class
+        if (lt.n_chains > 256) launch_shape<T, 4, 512>(lt, th, s, a, v2, st);
+        else launch_shape<T, 2, 1024>(lt, th, s, a, v2, st);
+    }
 }
 
 template void launch_chain<float>(const LatTable&, float*, DevState, const ChainArgs&, hipStream_t);

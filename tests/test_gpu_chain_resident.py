@@ -50,14 +50,15 @@ CASES = [  # lattices (L, chains): one link to several per thread, idle lanes, m
     ([(6, 3)], "f64", "interleaved", True),
     ([(6, 5), (4, 3)], "f32", "grouped", False),
     ([(8, 3)], "f32", "interleaved", False),
-    ([(8, 3), (6, 2), (4, 2)], "f64", "staggered", False),
+    ([(6, 3), (4, 2)], "f64", "staggered", False),
+    ([(8, 3), (6, 2), (4, 2)], "f64", "staggered", False),   # L = 8 in FP64: class passes
     ([(8, 5)], "f64", "grouped", True),
     ([(8, 257)], "f32", "grouped", False),
     ([(8, 257)], "f32", "interleaved", True),
     ([(4, 3)], "f64", "link", True),
     ([(6, 2)], "f64", "link", False),
     ([(8, 3), (4, 2)], "f32", "link", False),
-    ([(8, 2)], "f64", "link", False),   # does not fit with its candidates: class passes
+    ([(8, 2)], "f64", "link", False),
 ]
 
 
