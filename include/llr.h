@@ -190,10 +190,11 @@ llr_status llr_set_restriction(llr_ctx *ctx, int per_link);
  *     first, then the heatbath of colours 0..7 (the grouped order's passes
  *     continued half a sweep later; overrelaxation leaves E unchanged, so
  *     every chain's sweep still ends with the E of its heatbath half).  The
- *     two chain sets share no link and run on two streams (the context's and
- *     a second one of default priority, joined at the end of each sweep), so
- *     the heatbath passes, bound by vector instructions, overlap the
- *     overrelaxation passes, bound by memory.  2 x 4V link updates per
+ *     two chain sets share no link: in large runs they run on two streams (the
+ *     context's and a second one of default priority), so that the heatbath
+ *     passes, bound by vector instructions, overlap the overrelaxation passes,
+ *     bound by memory; in small ones on the context's stream, one set's
+ *     overrelaxation joined with the other's of the next sweep.  2 x 4V link updates per
  *     sweep, as grouped.
  * Applies to the restricted, free and multicanonical sweeps of llr_run /
  * llr_rm_step / llr_sweeps / llr_observables / the multicanonical run (whose

@@ -731,6 +731,46 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
     return LLR_OK;
 }
 
+// Whether staggered sweeps below the size of the pipelined ones run on one stream.
+// The second half's overrelaxation of a sweep then joins the first half's of the
+// sweep before: between them lies only the sweep's end, which neither depends on nor
+// changes (a recompute keeps them apart).  16 whole launches per sweep instead of 32
+// half ones on two streams; us per sweep two streams / one, FP32:
+// L = 12 x 16 159..178 / 118, 10 x 32 156..171 / 119, 14 x 20 152..173 / 145, 20 x 8
+// 170 / 162, 12 x 64 171 / 172, 14 x 39 183 / 188; FP64: 8 x 64 204 / 172, 10 x 32
+// 216 / 194, 20 x 2 223 / 197.
+static bool merged_stagger(const llr_ctx* c, int mode) {
+    return c->stagger && plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode);
+}
+
+template <typename T>
+static llr_status enqueue_merged_stagger(llr_ctx* c, int mode, const SweepRun& r) {
+    const LatTable ha = chain_part(c->lt, 0, 2), hb = chain_part(c->lt, 1, 2);
+    const uint32_t k0 = (uint32_t)c->prm.seed, k1 = (uint32_t)(c->prm.seed >> 32);
+    const int n = c->lt.n_chains;
+    const auto relax = [&](const LatTable& t) {
+        for (int col = 0; col < 8 && t.n_chains > 0; ++col) launch_or_pass<T>(t, (T*)c->state, c->ds, col, 0, c->stream);
+    };
+    relax(hb);
+    for (int t = 0; t < r.n; ++t) {
+        const bool rec = r.recompute(t);
+        for (int col = 0; col < 8; ++col)
+            launch_hb_pass<T>(c->lt, (T*)c->state, c->ds, col, mode, kSweep, k0, k1, c->stream);
+        if (rec) {
+            relax(ha);
+            launch_energy<T>(c->lt, (T*)c->state, c->ds, c->stream, false, recompute_check(mode));
+        }
+        launch_end_sweep(c->lt, c->ds, r.replica ? 1 : 0, t >= r.measure_from ? 1 : 0, 0, 1, k0, k1,
+                         r.E_hist ? r.E_hist + (size_t)t * n : nullptr,
+                         r.bits_hist ? r.bits_hist + (size_t)t * n : nullptr, c->stream);
+        if (t + 1 < r.n) relax(rec ? hb : c->lt);
+        else if (!rec) relax(ha);
+        note_sweep(c, false);
+        if ((t & 127) == 127) HIPCHK(hipStreamSynchronize(c->stream));   // bound the queue depth
+    }
+    return LLR_OK;
+}
+
 // the heatbath mode of Algorithm 1's restricted sweeps
 static int restricted_mode(const llr_ctx* c) { return c->per_link ? LLR_MODE_LINK : LLR_MODE_RESTRICTED; }
 
@@ -966,6 +1006,7 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
     // without replica exchange nothing couples the chains between sweeps
     const bool chunks = resident_sweeps(c, restricted_mode(c)) && !p.replica_exchange;
     const bool pipe = pipelined_sweeps(c, restricted_mode(c));
+    const bool merged = !pipe && merged_stagger(c, restricted_mode(c));
     for (int it = 0; it < iters; ++it) {
         for (int j = 0; chunks && j < nsw; j += kChainSweeps) {
             ChainArgs a = chain_args(c, restricted_mode(c), std::min(kChainSweeps, nsw - j));
@@ -976,12 +1017,13 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
             enqueue_chain<T>(c, a);
             if ((j / kChainSweeps & 15) == 15) HIPCHK(hipStreamSynchronize(c->stream));   // bound the queue depth
         }
-        if (pipe) {
-            st = enqueue_pipelined<T>(c, restricted_mode(c),
-                                      {nsw, 0, K, nsw - 1, p.n_th, p.replica_exchange != 0, nullptr, nullptr});
+        if (pipe || merged) {
+            const SweepRun r{nsw, 0, K, nsw - 1, p.n_th, p.replica_exchange != 0, nullptr, nullptr};
+            st = pipe ? enqueue_pipelined<T>(c, restricted_mode(c), r)
+                      : enqueue_merged_stagger<T>(c, restricted_mode(c), r);
             if (st != LLR_OK) return st;
         }
-        for (int j = 0; !chunks && !pipe && j < nsw; ++j) {
+        for (int j = 0; !chunks && !pipe && !merged && j < nsw; ++j) {
             const bool rec = ((j + 1) % K == 0) || (j == nsw - 1);
             st = launch_sweep<T>(c, rec, p.replica_exchange != 0, j >= p.n_th);
             if (st != LLR_OK) return st;
@@ -1042,13 +1084,15 @@ static llr_status plain_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, int m
     }
     const bool chunks = resident_sweeps(c, mode) && mode != LLR_MODE_APPROACH;
     const bool pipe = pipelined_sweeps(c, mode);
+    const bool merged = !pipe && merged_stagger(c, mode);
     for (int t0 = 0; t0 < n_sweeps; t0 += rows) {
         const int m = std::min(rows, n_sweeps - t0);
-        if (pipe) {
-            const llr_status st = enqueue_pipelined<T>(c, mode, {m, t0, K, -1, m, false, dE, dB});
+        if (pipe || merged) {
+            const SweepRun r{m, t0, K, -1, m, false, dE, dB};
+            const llr_status st = pipe ? enqueue_pipelined<T>(c, mode, r) : enqueue_merged_stagger<T>(c, mode, r);
             if (st != LLR_OK) return st;
         }
-        for (int t = 0; !pipe && t < m;) {
+        for (int t = 0; !pipe && !merged && t < m;) {
             double* eRow = dE ? dE + (size_t)t * n : nullptr;
             uint16_t* bRow = dB ? dB + (size_t)t * n : nullptr;
             if (chunks) {
