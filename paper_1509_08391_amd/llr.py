@@ -325,7 +325,7 @@ class Context:
         every colour), SWEEP_INTERLEAVED (heatbath then overrelaxation per
         colour, fused in one launch) or SWEEP_STAGGERED (grouped on the first
         half of each lattice's chains, overrelaxation first on the others,
-        the two halves on two streams)."""
+        in large runs on two streams)."""
         _check(lib().llr_set_sweep_order(self.h, int(order)))
 
     def set_tiles(self, hb_lpt, or_lpt):
