@@ -48,7 +48,9 @@ struct Chunk {
     float y[kRows];
 };
 
-// Forward of rows [0, nr) of a block of samples.
+// Forward of rows [0, nr) of a block of samples; the layers of the rows past it are
+// 0, also where a weight is infinite (tanh(inf 0 + b) is not a number, and the
+// gradient's sums run over all rows).
 __device__ void fwd_chunk(const Net& w, Chunk& c, const float* __restrict__ u, const float* __restrict__ invL, int row0,
                           int nr, int bf16) {
     const int t = threadIdx.x;
@@ -90,7 +92,10 @@ __device__ void fwd_chunk(const Net& w, Chunk& c, const float* __restrict__ u, c
                 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[ks], bv, acc, 0, 0, 0);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) c.h2[rt + 4 * kq + r][j] = tanhf(acc[r] + w.b2[j]);
+            for (int r = 0; r < 4; ++r) {
+                const int i = rt + 4 * kq + r;
+                c.h2[i][j] = i < nr ? tanhf(acc[r] + w.b2[j]) : 0.f;
+            }
         }
     } else {
         // 2 rows x 4 columns per thread, the sum over k in order
@@ -114,8 +119,8 @@ __device__ void fwd_chunk(const Net& w, Chunk& c, const float* __restrict__ u, c
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            c.h2[i0][jg + 16 * q] = tanhf(z[0][q]);
-            c.h2[i0 + 1][jg + 16 * q] = tanhf(z[1][q]);
+            c.h2[i0][jg + 16 * q] = i0 < nr ? tanhf(z[0][q]) : 0.f;
+            c.h2[i0 + 1][jg + 16 * q] = i0 + 1 < nr ? tanhf(z[1][q]) : 0.f;
         }
     }
     __syncthreads();
@@ -248,7 +253,7 @@ __global__ __launch_bounds__(kMB) void k_mlp_epoch(MlpBuf in, MlpBuf out, const 
     }
     __syncthreads();
     // output layer, biases and the loss, on a wavefront each; the rows past the
-    // last sample hold zeros (dy, d2, d1, lpart), so every sum runs over all rows
+    // last sample hold zeros (dy, h2, d2, d1, lpart), so every sum runs over all rows
     // with its loads issued ahead
     if (t < H) {
         float s = 0.f;
