@@ -38,11 +38,12 @@ __device__ __forceinline__ void scan_lnrho(const double* __restrict__ a, int n, 
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
                     v = __fma_rn(f, t[q], v);
+                    if (q == 0 && k0 + i == 0) v = 0.0;   // the first centre's by definition, also for an infinite s
                     term[i + q] = v;
                 }
             }
             for (; i < m; ++i) {
-                v = __fma_rn(f, term[i], v);
+                v = k0 + i == 0 ? 0.0 : __fma_rn(f, term[i], v);
                 term[i] = v;
             }
         }

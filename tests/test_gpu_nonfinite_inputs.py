@@ -32,3 +32,16 @@ def test_gradient_with_an_infinite_weight(n, bf16):
     terms = 0.2 * (pred - a) / n * np.sign(h1)
     assert np.isfinite(loss)
     assert abs(g[OW3 + 3] - terms.sum()) < 1e-6 * np.abs(terms).sum()
+
+
+@pytest.mark.parametrize("n", [1, 5, 16, 512, 513, 1100])
+def test_ln_rho_with_an_infinite_width(n):
+    """ln rho of the first interval is 0 by definition, whatever the width; the others
+    then lie infinitely below it, and every moment is the first interval's."""
+    from paper_1509_08391_amd import llr
+    ctx = llr.Context(precision=llr.FP64)
+    c = 0.6 + 0.01 * np.arange(n)
+    lr, u, cv = ctx.reconstruct(c, np.full(n, 1.01), np.inf, 1.0, [1.0])
+    ctx.close()
+    assert lr[0] == 0.0 and np.all(lr[1:] == -np.inf)
+    assert u[0] == c[0] and cv[0] == 0.0
