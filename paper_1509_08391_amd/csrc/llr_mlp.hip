@@ -48,9 +48,7 @@ struct Chunk {
     float y[kRows];
 };
 
-// Forward of rows [0, nr) of a block of samples; the layers of the rows past it are
-// 0, also where a weight is infinite (tanh(inf 0 + b) is not a number, and the
-// gradient's sums run over all rows).
+// Forward of rows [0, nr) of a block of samples.
 __device__ void fwd_chunk(const Net& w, Chunk& c, const float* __restrict__ u, const float* __restrict__ invL, int row0,
                           int nr, int bf16) {
     const int t = threadIdx.x;
@@ -92,10 +90,7 @@ __device__ void fwd_chunk(const Net& w, Chunk& c, const float* __restrict__ u, c
                 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[ks], bv, acc, 0, 0, 0);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = rt + 4 * kq + r;
-                c.h2[i][j] = i < nr ? tanhf(acc[r] + w.b2[j]) : 0.f;
-            }
+            for (int r = 0; r < 4; ++r) c.h2[rt + 4 * kq + r][j] = tanhf(acc[r] + w.b2[j]);
         }
     } else {
         // 2 rows x 4 columns per thread, the sum over k in order
@@ -119,8 +114,8 @@ __device__ void fwd_chunk(const Net& w, Chunk& c, const float* __restrict__ u, c
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            c.h2[i0][jg + 16 * q] = i0 < nr ? tanhf(z[0][q]) : 0.f;
-            c.h2[i0 + 1][jg + 16 * q] = i0 + 1 < nr ? tanhf(z[1][q]) : 0.f;
+            c.h2[i0][jg + 16 * q] = tanhf(z[0][q]);
+            c.h2[i0 + 1][jg + 16 * q] = tanhf(z[1][q]);
         }
     }
     __syncthreads();
@@ -250,6 +245,8 @@ __global__ __launch_bounds__(kMB) void k_mlp_epoch(MlpBuf in, MlpBuf out, const 
     for (int e = t; e < kRows * H; e += kMB) {
         const int i = e / H, k = e - i * H;
         d2[i][k] = i < nr ? dy[i] * net.w3[k] * (1.f - c.h2[i][k] * c.h2[i][k]) : 0.f;
+        // (tanh(0 w + b2) in the rows past the last sample: not a number for an infinite w)
+        if (i >= nr) c.h2[i][k] = 0.f;
     }
     __syncthreads();
     // output layer, biases and the loss, on a wavefront each; the rows past the
