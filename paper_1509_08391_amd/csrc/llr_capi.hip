@@ -168,7 +168,8 @@ struct Xfer {
     bool pinned;
     size_t used = 0, up = 0;              // bytes laid out; end of the inputs
     struct Out { void* dst; size_t off, n; };
-    std::vector<Out> outs;
+    Out outs[4];                          // no memory of its own: llr_beta_c_noalloc allocates nothing
+    int n_outs = 0;
     hipError_t err = hipSuccess;
 
     // bytes: of all inputs and outputs together (rounded up to 8 each)
@@ -191,25 +192,29 @@ struct Xfer {
     P* out(P* dst, size_t count) {
         const size_t n = count * sizeof(P), at = used;
         used += (n + 7) & ~(size_t)7;
-        if (dst && n) outs.push_back({dst, at, n});
+        if (dst && n) {
+            if (n_outs < 4) outs[n_outs++] = {dst, at, n};
+            else err = hipErrorInvalidValue;
+        }
         return (P*)(dev + at);
     }
     // outputs to the host; ends with the stream synchronised
     llr_status download() {
         if (pinned) {
-            if (!outs.empty()) {
-                const size_t lo = outs.front().off, hi = outs.back().off + outs.back().n;
+            if (n_outs > 0 && err == hipSuccess) {
+                const size_t lo = outs[0].off, hi = outs[n_outs - 1].off + outs[n_outs - 1].n;
                 err = hipMemcpyAsync(c->pin + lo, dev + lo, hi - lo, hipMemcpyDeviceToHost, c->stream);
             }
         } else {
-            for (const auto& o : outs)
-                if (err == hipSuccess) err = hipMemcpyAsync(o.dst, dev + o.off, o.n, hipMemcpyDeviceToHost, c->stream);
+            for (int i = 0; i < n_outs; ++i)
+                if (err == hipSuccess)
+                    err = hipMemcpyAsync(outs[i].dst, dev + outs[i].off, outs[i].n, hipMemcpyDeviceToHost, c->stream);
         }
         if (err == hipSuccess) err = hipStreamSynchronize(c->stream);
         if (err == hipSuccess) err = hipGetLastError();
         if (err != hipSuccess) return fail(LLR_EDEVICE, std::string("download: ") + hipGetErrorString(err));
         if (pinned)
-            for (const auto& o : outs) memcpy(o.dst, c->pin + o.off, o.n);
+            for (int i = 0; i < n_outs; ++i) memcpy(outs[i].dst, c->pin + outs[i].off, outs[i].n);
         return LLR_OK;
     }
 };

@@ -1,0 +1,22 @@
+"""What the library's calls ask of the runtime, seen on the CPU: libllr.so against
+a recorder in the runtime's place (no kernel runs)."""
+from tests.hip_recorder import run
+
+
+def test_beta_c_noalloc_allocates_nothing(tmp_path):
+    """Neither device nor host memory, also where inputs exceed the pinned buffer
+    (n = 5000); the allocating call is there to show that the counters count."""
+    got = run(tmp_path, '''
+h = context()
+result = []
+for n in (128, 5000):
+    c, a = 1000.0 + np.arange(n), np.full(n, 1.01)
+    bc, pk = C.c_double(), C.c_double()
+    for f in (L.llr_beta_c, L.llr_beta_c_noalloc):
+        rec.rec_reset()
+        st = f(h, dptr(c), dptr(a), n, 1.0, 1e4, 1.0, 1.01, 1e-5, 1e-9, C.byref(bc), C.byref(pk))
+        result.append([st, rec.rec_news(), sum(k[0] in ("hipMalloc", "hipHostMalloc") for k in calls())])
+''')
+    assert [g[0] for g in got] == [0, 0, 0, 0]
+    assert got[0][2] == 1 and got[2][2] == 1
+    assert got[1][1:] == [0, 0] and got[3][1:] == [0, 0], got
