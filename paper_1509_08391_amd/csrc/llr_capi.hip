@@ -2013,6 +2013,7 @@ llr_status llr_prob_peaks(llr_ctx* c, const double* centres, const double* a, in
         return fail(LLR_EINVAL, "bad argument");
     if (!uniform_centres(centres, n, s)) return fail(LLR_EINVAL, "centres must be spaced by s");
     HIPCHK(hipSetDevice(c->device));
+    max_peaks = std::min(max_peaks, n);   // each lies between two intervals
     const size_t bytes = 8 * (2 * (size_t)n + 2 * (size_t)max_peaks + 1);
     llr_status st = ensure_stage(c, bytes + 8 * ((size_t)n + 2) + 64);
     if (st != LLR_OK) return st;

@@ -20,3 +20,20 @@ for n in (128, 5000):
     assert [g[0] for g in got] == [0, 0, 0, 0]
     assert got[0][2] == 1 and got[2][2] == 1
     assert got[1][1:] == [0, 0] and got[3][1:] == [0, 0], got
+
+
+def test_prob_peaks_room_follows_the_intervals(tmp_path):
+    """n intervals have fewer than n interior maxima, so a caller's larger max_peaks
+    asks for no more memory than n does, on either side."""
+    got = run(tmp_path, '''
+result = []
+n = 40
+c, a = 1000.0 + np.arange(n), np.full(n, 1.01)
+E, lp, nf = np.zeros(n), np.zeros(n), C.c_int()
+for peaks in (n, 1 << 22):
+    h = context()
+    rec.rec_reset()
+    st = L.llr_prob_peaks(h, dptr(c), dptr(a), n, 1.0, 1.01, peaks, dptr(E), dptr(lp), C.byref(nf))
+    result.append([st, rec.rec_new_max(), sum(k[3] for k in calls() if k[0] != "launch")])
+''')
+    assert got[0] == got[1], got
