@@ -676,9 +676,7 @@ struct SweepRun {
 };
 
 template <typename T>
-static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
-    llr_status st = ensure_side_stream(c);
-    if (st != LLR_OK) return st;
+static llr_status pipelined_run(llr_ctx* c, int mode, const SweepRun& r) {
     const LatTable ha = chain_part(c->lt, 0, 2), hb = chain_part(c->lt, 1, 2);
     const std::vector<LatTable> pa = pipe_parts(c, ha), pb = pipe_parts(c, hb);
     const uint32_t k0 = (uint32_t)c->prm.seed, k1 = (uint32_t)(c->prm.seed >> 32);
@@ -734,6 +732,17 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
     HIPCHK(hipEventRecord(c->join_ev, c->side));
     HIPCHK(hipStreamWaitEvent(c->stream, c->join_ev, 0));
     return LLR_OK;
+}
+
+// On an error in the middle of the run the streams are not joined: what the second one
+// still has is waited for, so that nothing runs beside the caller's next call.
+template <typename T>
+static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
+    llr_status st = ensure_side_stream(c);
+    if (st != LLR_OK) return st;
+    st = pipelined_run<T>(c, mode, r);
+    if (st != LLR_OK) hipStreamSynchronize(c->side);
+    return st;
 }
 
 // Whether staggered sweeps below the size of the pipelined ones run on one stream.

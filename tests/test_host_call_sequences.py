@@ -37,3 +37,29 @@ for peaks in (n, 1 << 22):
     result.append([st, rec.rec_new_max(), sum(k[3] for k in calls() if k[0] != "launch")])
 ''')
     assert got[0] == got[1], got
+
+
+def test_error_in_halves_leaves_no_work_on_the_second_stream(tmp_path):
+    """Each event call of an iteration in two halves made to fail in turn: the call
+    reports it, and waits for what it has put on its second stream."""
+    got = run(tmp_path, '''
+result = []
+for order in (llr.SWEEP_GROUPED, llr.SWEEP_INTERLEAVED, llr.SWEEP_STAGGERED):
+    h = context(llr.FP32, [(16, 25)], order, n_th=2, n_a=4)
+    assert L.llr_rm_begin(h) == 0
+    rec.rec_reset()
+    assert L.llr_rm_step(h, 1) == 0
+    done = calls()
+    for op in ("hipEventRecord", "hipStreamWaitEvent"):
+        for at in range(sum(k[0] == op for k in done)):
+            rec.rec_reset()
+            rec.rec_fail(op.encode(), at)
+            st = L.llr_rm_step(h, 1)
+            left = 0
+            for kind, name, stream, _ in calls():
+                if stream != 0x77 and kind == "launch": left += 1
+                if stream != 0x77 and kind == "hipStreamSynchronize": left = 0
+            result.append([st, left])
+''')
+    assert len(got) > 60 and all(st == -3 for st, _ in got), got
+    assert all(left == 0 for _, left in got), got
