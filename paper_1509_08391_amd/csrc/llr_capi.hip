@@ -2239,19 +2239,20 @@ llr_status llr_mlp_warm_start(llr_ctx* c, int lat, const float* w, int bf16, dou
 
 // Device workspace of the training behind the inputs of stage_inputs: two sets
 // of parameters and moments, two of the chunks' partial gradients, the chunks'
-// parts of every epoch's loss and the losses.
+// parts of the losses of one block of epochs and the losses.
+constexpr int kLossEpochs = 256;   // summed by one launch; bounds the parts
 struct MlpWork {
     MlpBuf buf[2];
     float* part[2];
     double *loss_part, *loss;
     static size_t bytes(int n, int epochs) {
         const size_t nc = (size_t)mlp_chunks(n);
-        return 4 * (size_t)kMlpNP * (6 + 2 * nc) + 8 * (size_t)epochs * (nc + 1) + 64;
+        return 4 * (size_t)kMlpNP * (6 + 2 * nc) + 8 * ((size_t)std::min(epochs, kLossEpochs) * nc + (size_t)epochs) + 64;
     }
     MlpWork(void* base, int n, int epochs) {
         const size_t nc = (size_t)mlp_chunks(n);
         loss_part = (double*)(((uintptr_t)base + 7) & ~(uintptr_t)7);
-        loss = loss_part + (size_t)epochs * nc;
+        loss = loss_part + (size_t)std::min(epochs, kLossEpochs) * nc;
         float* p = (float*)(loss + epochs);
         for (auto& b : buf) {
             b = {p, p + kMlpNP, p + 2 * kMlpNP};
@@ -2306,12 +2307,14 @@ llr_status llr_mlp_train(llr_ctx* c, float* w, const float* u, const float* invL
     int cur = 0;
     for (int e = 0; e < epochs; ++e) {
         const int t = in_epoch ? e : 0;
+        const int el = e % kLossEpochs;
         launch_mlp_epoch(k.buf[cur], k.buf[cur ^ 1], k.part[(e + 1) & 1], t, lr, du, dl, dA, n, bf16, k.part[e & 1],
-                         k.loss_part + (size_t)e * nc, c->stream);
+                         k.loss_part + (size_t)el * nc, c->stream);
+        if (el == kLossEpochs - 1 || e == epochs - 1)
+            launch_mlp_loss(k.loss_part, n, el + 1, k.loss + (e - el), c->stream);
         if (t > 0) cur ^= 1;
         if (!in_epoch || e == epochs - 1) launch_mlp_adam(k.buf[cur], k.buf[cur], k.part[e & 1], n, e + 1, lr, c->stream);
     }
-    if (epochs > 0) launch_mlp_loss(k.loss_part, n, epochs, k.loss, c->stream);
     HIPCHK(hipMemcpyAsync(w, k.buf[cur].w, 4 * kMlpNP, hipMemcpyDeviceToHost, c->stream));
     if (loss_hist && epochs > 0) HIPCHK(hipMemcpyAsync(loss_hist, k.loss, 8 * (size_t)epochs, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));

@@ -1,0 +1,76 @@
+"""Captured sweeps at a size that runs them: L = 10 with a few chains is neither
+kept in LDS nor large enough for two halves, so its grouped and interleaved sweeps
+are class passes replayed from HIP graphs.  Replays over several Robbins-Monro
+iterations, with the host's reads in between, against direct launches, and a
+switch of the order or of the restriction between iterations: the same launches,
+so every result is equal bit for bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+L, N = 10, 5
+
+
+def _context(prec, replica, graphs, n_rm=4):
+    from paper_1509_08391_amd import llr
+    v6 = 6 * L ** 4
+    dE = 0.02 * v6
+    ctx = llr.Context(precision=llr.FP32 if prec == "f32" else llr.FP64)
+    ctx.set_params(n_th=2, n_a=5, n_rm=n_rm, seed=23, replica_exchange=replica, recompute_every=3, approach_cap=4000)
+    ctx.add_lattice(L, 0.6 * v6 + dE * np.arange(N), dE)
+    ctx.bind_state()
+    ctx.set_a(0, 1.0)
+    ctx.set_graphs(graphs)
+    ctx.hot_start()
+    ctx.approach()
+    ctx.set_tiles(4, 2)
+    ctx.enable_bits_log(64)
+    return ctx
+
+
+def _results(ctx):
+    return [ctx.get_history(0), ctx.get_bits_log(), ctx.export_state(0).cpu().numpy(), *ctx.get_energy(0), *ctx.stats()]
+
+
+@pytest.mark.parametrize("replica", [False, True])
+@pytest.mark.parametrize("order", ["grouped", "interleaved"])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_replays_equal_direct_launches(prec, order, replica):
+    from paper_1509_08391_amd import llr
+    got = []
+    for graphs in (True, False):
+        ctx = _context(prec, replica, graphs)
+        ctx.set_sweep_order({"grouped": llr.SWEEP_GROUPED, "interleaved": llr.SWEEP_INTERLEAVED}[order])
+        ctx.rm_begin()
+        E = []
+        for _ in range(4):
+            ctx.rm_step(1)
+            E.append(ctx.get_energy(0)[0])
+            ctx.recompute_energy()
+        got.append([np.array(E)] + _results(ctx))
+        ctx.close()
+    assert got[0][2].any()
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("switch", ["order", "restriction"])
+def test_switch_between_iterations(switch, prec):
+    from paper_1509_08391_amd import llr
+    got = []
+    for graphs in (True, False):
+        ctx = _context(prec, True, graphs)
+        ctx.rm_begin()
+        ctx.rm_step(1)
+        for on in (True, False, True):
+            if switch == "order":
+                ctx.set_sweep_order(llr.SWEEP_INTERLEAVED if on else llr.SWEEP_GROUPED)
+            else:
+                ctx.set_restriction(on)
+            ctx.rm_step(1)
+        got.append(_results(ctx))
+        ctx.close()
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)

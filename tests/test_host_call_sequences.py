@@ -63,3 +63,22 @@ for order in (llr.SWEEP_GROUPED, llr.SWEEP_INTERLEAVED, llr.SWEEP_STAGGERED):
 ''')
     assert len(got) > 60 and all(st == -3 for st, _ in got), got
     assert all(left == 0 for _, left in got), got
+
+
+def test_training_workspace_does_not_grow_with_epochs(tmp_path):
+    """Beyond the losses themselves, 8 bytes an epoch."""
+    got = run(tmp_path, '''
+result = []
+fp = C.POINTER(C.c_float)
+n = 4096
+w, u, il, a = np.zeros(llr.N_PARAMS, np.float32), np.full(n, 0.6, np.float32), np.full(n, 0.1, np.float32), np.ones(n)
+for epochs in (1000, 5000):
+    h = context()
+    rec.rec_reset()
+    hist = np.zeros(epochs)
+    st = L.llr_mlp_train(h, w.ctypes.data_as(fp), u.ctypes.data_as(fp), il.ctypes.data_as(fp), dptr(a), n, epochs, 1e-3,
+                         1, dptr(hist))
+    result.append([st, sum(k[3] for k in calls() if k[0] == "hipMalloc")])
+''')
+    assert got[0][0] == got[1][0] == 0
+    assert got[1][1] - got[0][1] == 8 * 4000, got
