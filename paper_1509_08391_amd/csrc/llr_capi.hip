@@ -631,16 +631,35 @@ static llr_status ensure_side_stream(llr_ctx* c);
 // 8 154 / 160.  Three or four sets on as many streams are slower than one (14 x 74:
 // 256, 260). (One captured graph per period of sweeps made the halves slower: 1198
 // instead of 1180 us at L = 20 x 128.)
-static bool pipelined_sweeps(const llr_ctx* c, int mode) {
-    if (!plain_mode(mode) || c->timing || !c->use_graphs || resident_sweeps(c, mode))
-        return false;
+static long long run_links(const llr_ctx* c) {   // FP64 ones counted four times
     long long links = 0;
-    bool two = false;
-    for (int i = 0; i < c->lt.n; ++i) {
-        links += (long long)c->lt.l[i].n_chains * c->lt.l[i].V2;
-        two = two || c->lt.l[i].n_chains > 1;
-    }
-    return two && links * (c->precision == LLR_FP32 ? 1 : 4) >= kPipeLinks;
+    for (int i = 0; i < c->lt.n; ++i) links += (long long)c->lt.l[i].n_chains * c->lt.l[i].V2;
+    return links * (c->precision == LLR_FP32 ? 1 : 4);
+}
+static bool two_halves(const llr_ctx* c) {
+    for (int i = 0; i < c->lt.n; ++i)
+        if (c->lt.l[i].n_chains > 1) return true;
+    return false;
+}
+static bool large_sweeps(const llr_ctx* c, int mode) {
+    return plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode) && two_halves(c) &&
+           run_links(c) >= kPipeLinks;
+}
+
+// Whether a run of n such sweeps is long enough.  In the grouped order the second half
+// starts half a sweep late, which the gain of the n - 1 sweeps after it has to make up
+// for; in the others the halves only pay for their first ramp.  The smaller the run,
+// the smaller its gain per sweep.  Us per sweep of an iteration whole / in halves: grouped, L =
+// 12 x 20 FP64 (830 000 links as counted) 240 / 370 for n = 1, 220 / 233 for 4, 218 / 218 for
+// 6; 14 x 40 FP32 (768 000) 222 / 315, 194 / 198 and 192 / 186; 16 x 64 FP32 (2.1
+// million) 381 / 465 for 1, 340 / 328 for 3; 18 x 96 FP32 (5.0 million) 736 / 823 for 1,
+// 677 / 677 for 2; 20 x 128 FP32 1450 / 1424 for 1.  Interleaved, 14 x 40 FP32 171 / 214
+// for 1, 144 / 145 for 4; 16 x 64 FP32 282 / 292 for 1, 252 / 237 for 2; staggered, 12 x
+// 80 FP32 263 / 277 for 1, 206 / 202 for 3.
+constexpr long long kPipeLateLinks = 3800000, kPipeRunLinks = 2500000;
+static bool pipelined_sweeps(const llr_ctx* c, int mode, int n) {
+    if (!large_sweeps(c, mode)) return false;
+    return c->interleave || c->stagger ? run_links(c) * n >= kPipeRunLinks : run_links(c) * (n - 1) >= kPipeLateLinks;
 }
 
 // The parts of a half that go through their sweep one after another, each its
@@ -754,7 +773,8 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
 // 170 / 162, 12 x 64 171 / 172, 14 x 39 183 / 188; FP64: 8 x 64 204 / 172, 10 x 32
 // 216 / 194, 20 x 2 223 / 197.
 static bool merged_stagger(const llr_ctx* c, int mode) {
-    return c->stagger && plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode);
+    return c->stagger && plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode) &&
+           !large_sweeps(c, mode);
 }
 
 template <typename T>
@@ -1019,7 +1039,7 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
     llr_status st = LLR_OK;
     // without replica exchange nothing couples the chains between sweeps
     const bool chunks = resident_sweeps(c, restricted_mode(c)) && !p.replica_exchange;
-    const bool pipe = pipelined_sweeps(c, restricted_mode(c));
+    const bool pipe = pipelined_sweeps(c, restricted_mode(c), nsw);
     const bool merged = !pipe && merged_stagger(c, restricted_mode(c));
     for (int it = 0; it < iters; ++it) {
         for (int j = 0; chunks && j < nsw; j += kChainSweeps) {
@@ -1097,7 +1117,7 @@ static llr_status plain_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, int m
         if (bits) dB = (uint16_t*)((char*)c->stage + (E_hist ? 8 * (size_t)rows * n : 0));
     }
     const bool chunks = resident_sweeps(c, mode) && mode != LLR_MODE_APPROACH;
-    const bool pipe = pipelined_sweeps(c, mode);
+    const bool pipe = pipelined_sweeps(c, mode, n_sweeps);
     const bool merged = !pipe && merged_stagger(c, mode);
     for (int t0 = 0; t0 < n_sweeps; t0 += rows) {
         const int m = std::min(rows, n_sweeps - t0);

@@ -82,3 +82,28 @@ for epochs in (1000, 5000):
 ''')
     assert got[0][0] == got[1][0] == 0
     assert got[1][1] - got[0][1] == 8 * 4000, got
+
+
+def test_short_runs_stay_whole(tmp_path):
+    """A run of a few sweeps is not split into halves: the second half has to wait for
+    the first to get ahead, and no later sweep makes up for it."""
+    got = run(tmp_path, '''
+result = {}
+for name, prec, lats, order, counts in (("g", llr.FP64, [(12, 20)], llr.SWEEP_GROUPED, (1, 2, 5, 6)),
+                                        ("i", llr.FP64, [(12, 20)], llr.SWEEP_INTERLEAVED, (1, 3, 4)),
+                                        ("G", llr.FP32, [(18, 96)], llr.SWEEP_GROUPED, (1, 2)),
+                                        ("I", llr.FP32, [(18, 96)], llr.SWEEP_INTERLEAVED, (1,))):
+    streams = []
+    for n in counts:
+        h = context(prec, lats, order, n_th=0, n_a=n)
+        assert L.llr_rm_begin(h) == 0
+        for f in (lambda: L.llr_sweeps(h, n, 3, llr.MODE_FREE, None), lambda: L.llr_rm_step(h, 1)):
+            rec.rec_reset()
+            assert f() == 0
+            # launches of a captured sweep go to the capturing stream
+            capturing = [k[2] for k in calls() if k[0] == "hipStreamBeginCapture"]
+            streams.append(len({k[2] for k in calls() if k[0] == "launch" and k[2] not in capturing}))
+        L.llr_destroy(h)
+    result[name] = streams
+''')
+    assert got == {"g": [1, 1, 1, 1, 1, 1, 2, 2], "i": [1, 1, 1, 1, 2, 2], "G": [1, 1, 2, 2], "I": [2, 2]}, got
