@@ -578,8 +578,10 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
         const LatTable ha = chain_part(c->lt, 0, 2), hb = chain_part(c->lt, 1, 2);
         const uint32_t k0 = (uint32_t)c->prm.seed, k1 = (uint32_t)(c->prm.seed >> 32);
         TimeScope ts(c, 0, 16);
-        hipEventRecord(c->fork_ev, c->stream);
-        hipStreamWaitEvent(c->side, c->fork_ev, 0);
+        if (hb.n_chains > 0) {
+            hipEventRecord(c->fork_ev, c->stream);
+            hipStreamWaitEvent(c->side, c->fork_ev, 0);
+        }
         for (int j = 0; j < 16; ++j) {
             const int col = j & 7;
             if (j < 8) launch_hb_pass<T>(ha, (T*)c->state, c->ds, col, mode, kSweep, k0, k1, c->stream);
@@ -588,8 +590,10 @@ static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bo
             if (j < 8) launch_or_pass<T>(hb, (T*)c->state, c->ds, col, 0, c->side);
             else launch_hb_pass<T>(hb, (T*)c->state, c->ds, col, mode, kSweep, k0, k1, c->side);
         }
-        hipEventRecord(c->join_ev, c->side);
-        hipStreamWaitEvent(c->stream, c->join_ev, 0);
+        if (hb.n_chains > 0) {
+            hipEventRecord(c->join_ev, c->side);
+            hipStreamWaitEvent(c->stream, c->join_ev, 0);
+        }
     } else {
         {
             TimeScope ts(c, 0, 8);
@@ -768,13 +772,15 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
 // The second half's overrelaxation of a sweep then joins the first half's of the
 // sweep before: between them lies only the sweep's end, which neither depends on nor
 // changes (a recompute keeps them apart).  16 whole launches per sweep instead of 32
-// half ones on two streams; us per sweep two streams / one, FP32:
+// half ones on two streams.  Lattices of one chain each have no second half, and their
+// grouped passes are replayed from captured graphs like the grouped order's (L = 10 x 1
+// FP32 99 / 86 us, direct / replayed).  Us per sweep two streams / one, FP32:
 // L = 12 x 16 159..178 / 118, 10 x 32 156..171 / 119, 14 x 20 152..173 / 145, 20 x 8
 // 170 / 162, 12 x 64 171 / 172, 14 x 39 183 / 188; FP64: 8 x 64 204 / 172, 10 x 32
 // 216 / 194, 20 x 2 223 / 197.
 static bool merged_stagger(const llr_ctx* c, int mode) {
     return c->stagger && plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode) &&
-           !large_sweeps(c, mode);
+           two_halves(c) && !large_sweeps(c, mode);
 }
 
 template <typename T>
@@ -783,7 +789,7 @@ static llr_status enqueue_merged_stagger(llr_ctx* c, int mode, const SweepRun& r
     const uint32_t k0 = (uint32_t)c->prm.seed, k1 = (uint32_t)(c->prm.seed >> 32);
     const int n = c->lt.n_chains;
     const auto relax = [&](const LatTable& t) {
-        for (int col = 0; col < 8 && t.n_chains > 0; ++col) launch_or_pass<T>(t, (T*)c->state, c->ds, col, 0, c->stream);
+        for (int col = 0; col < 8; ++col) launch_or_pass<T>(t, (T*)c->state, c->ds, col, 0, c->stream);
     };
     relax(hb);
     for (int t = 0; t < r.n; ++t) {

@@ -107,3 +107,17 @@ for name, prec, lats, order, counts in (("g", llr.FP64, [(12, 20)], llr.SWEEP_GR
     result[name] = streams
 ''')
     assert got == {"g": [1, 1, 1, 1, 1, 1, 2, 2], "i": [1, 1, 1, 1, 2, 2], "G": [1, 1, 2, 2], "I": [2, 2]}, got
+
+
+def test_staggered_order_of_single_chains_needs_one_stream(tmp_path):
+    """Without a second half there is nothing to fork: iterations replay their captured
+    sweeps, and direct launches stay on the context's stream."""
+    got = run(tmp_path, '''
+h = context(llr.FP32, [(10, 1), (12, 1)], llr.SWEEP_STAGGERED, n_th=1, n_a=3)
+assert L.llr_rm_begin(h) == 0
+rec.rec_reset()
+assert L.llr_rm_step(h, 1) == 0 and L.llr_sweeps(h, 2, 3, llr.MODE_FREE, None) == 0
+k = calls()
+result = [sum(x[0] == "hipGraphLaunch" for x in k), sum(x[0] == "hipStreamWaitEvent" for x in k)]
+''')
+    assert got == [4, 0], got
