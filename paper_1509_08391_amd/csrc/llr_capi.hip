@@ -96,6 +96,7 @@ struct llr_ctx {
     DevState ds{};
     bool laid_out = false;
     bool resident = false;     // every lattice's chain fits in LDS (chain-resident sweeps)
+    bool resident_wide = false;   // a chain of L = 8 among them
     bool resident_link = false;   // with a class's candidates of the per-link restriction too
     void* state = nullptr;
     size_t state_bytes = 0;
@@ -400,6 +401,8 @@ static llr_status layout(llr_ctx* c) {
     HIPCHK(hipMemcpyAsync(s.conf, ident.data(), n * 4, hipMemcpyHostToDevice, c->stream));
     c->resident = chain_fits(lt, elem_size(c), false);
     c->resident_link = chain_fits(lt, elem_size(c), true);
+    c->resident_wide = false;
+    for (const auto& hl : c->lats) c->resident_wide = c->resident_wide || hl.L >= 8;
     if (c->resident) HIPCHK(chain_setup());
     c->approach_sweeps.assign(lt.n, 0);
     c->laid_out = true;
@@ -516,9 +519,18 @@ static bool plain_mode(int mode) {
 
 // Whether sweeps of this mode run chain-resident: every chain fits in LDS and no
 // per-kernel timing is asked for (its figures are those of the class-pass
-// kernels).
-static bool resident_sweeps(const llr_ctx* c, int mode) {
-    return (mode == LLR_MODE_LINK ? c->resident_link : c->resident) && !c->timing;
+// kernels).  exchange: replica exchange after every sweep, which takes a launch per
+// sweep.  The interleaved order has 8 class passes a sweep instead of 16, and at L = 8
+// they are faster than one launch that loads and stores every chain (with exchange),
+// unless the chains give every CU something to do and no CU a second one.  Us per sweep
+// chain-resident / class passes, L = 8 FP32 interleaved with exchange: 3 chains 77 / 66,
+// 96 80 / 77, 128 80 / 82, 256 81 / 109, 258 141 / 114, 1024 278 / 191; without: 3
+// chains 60 / 65, 512 110 / 135, 768 173 / 155, 2048 427 / 309.
+static bool resident_sweeps(const llr_ctx* c, int mode, bool exchange = false) {
+    if (!(mode == LLR_MODE_LINK ? c->resident_link : c->resident) || c->timing) return false;
+    if (!c->interleave || !c->resident_wide || !plain_mode(mode)) return true;
+    const int n = c->lt.n_chains;
+    return exchange ? n >= 128 && n <= 256 : n <= 512;
 }
 
 static int recompute_check(int mode) {
@@ -554,7 +566,7 @@ constexpr long long kPipeLinks = 760000;
 template <typename T>
 static void enqueue_sweep(llr_ctx* c, int mode, bool recompute, bool replica, bool measure, double* E_row = nullptr,
                           uint16_t* b_row = nullptr) {
-    if (resident_sweeps(c, mode) && mode != LLR_MODE_APPROACH) {
+    if (resident_sweeps(c, mode, replica) && mode != LLR_MODE_APPROACH) {
         ChainArgs a = chain_args(c, mode, 1);
         a.every = recompute ? 1 : 0;
         a.end_sweep = 0;
@@ -645,8 +657,8 @@ static bool two_halves(const llr_ctx* c) {
         if (c->lt.l[i].n_chains > 1) return true;
     return false;
 }
-static bool large_sweeps(const llr_ctx* c, int mode) {
-    return plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode) && two_halves(c) &&
+static bool large_sweeps(const llr_ctx* c, int mode, bool exchange = false) {
+    return plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode, exchange) && two_halves(c) &&
            run_links(c) >= kPipeLinks;
 }
 
@@ -661,8 +673,8 @@ static bool large_sweeps(const llr_ctx* c, int mode) {
 // for 1, 144 / 145 for 4; 16 x 64 FP32 282 / 292 for 1, 252 / 237 for 2; staggered, 12 x
 // 80 FP32 263 / 277 for 1, 206 / 202 for 3.
 constexpr long long kPipeLateLinks = 3800000, kPipeRunLinks = 2500000;
-static bool pipelined_sweeps(const llr_ctx* c, int mode, int n) {
-    if (!large_sweeps(c, mode)) return false;
+static bool pipelined_sweeps(const llr_ctx* c, int mode, int n, bool exchange) {
+    if (!large_sweeps(c, mode, exchange)) return false;
     return c->interleave || c->stagger ? run_links(c) * n >= kPipeRunLinks : run_links(c) * (n - 1) >= kPipeLateLinks;
 }
 
@@ -1045,7 +1057,7 @@ static llr_status rm_step_impl(llr_ctx* c, int iters) {
     llr_status st = LLR_OK;
     // without replica exchange nothing couples the chains between sweeps
     const bool chunks = resident_sweeps(c, restricted_mode(c)) && !p.replica_exchange;
-    const bool pipe = pipelined_sweeps(c, restricted_mode(c), nsw);
+    const bool pipe = pipelined_sweeps(c, restricted_mode(c), nsw, p.replica_exchange != 0);
     const bool merged = !pipe && merged_stagger(c, restricted_mode(c));
     for (int it = 0; it < iters; ++it) {
         for (int j = 0; chunks && j < nsw; j += kChainSweeps) {
@@ -1123,7 +1135,7 @@ static llr_status plain_sweeps(llr_ctx* c, int n_sweeps, long long sweep0, int m
         if (bits) dB = (uint16_t*)((char*)c->stage + (E_hist ? 8 * (size_t)rows * n : 0));
     }
     const bool chunks = resident_sweeps(c, mode) && mode != LLR_MODE_APPROACH;
-    const bool pipe = pipelined_sweeps(c, mode, n_sweeps);
+    const bool pipe = pipelined_sweeps(c, mode, n_sweeps, false);
     const bool merged = !pipe && merged_stagger(c, mode);
     for (int t0 = 0; t0 < n_sweeps; t0 += rows) {
         const int m = std::min(rows, n_sweeps - t0);

@@ -20,7 +20,7 @@ def _context(llr, lats, prec, order, stream=None, replica=False, **params):
                              "staggered": llr.SWEEP_STAGGERED}[order])
     for L, n in lats:
         v6 = 6 * L ** 4
-        lo, hi = (0.5, 0.72) if L <= 6 else (0.58, 0.68)
+        lo, hi = (0.5, 0.72) if L <= 8 else (0.58, 0.68)
         dE = (hi - lo) / n * v6
         ctx.add_lattice(L, lo * v6 + dE * np.arange(n), dE)
     ctx.bind_state()
@@ -136,4 +136,22 @@ def test_histories_of_several_blocks_in_halves(order):
         got.append([ctx.muca_sweeps(3300, sweep0=5), ctx.export_state(0).cpu().numpy(), ctx.get_energy(0)[0]])
         ctx.close()
     assert np.ptp(got[0][0][:, 0]) > 0
+    _equal(*got)
+
+
+@pytest.mark.parametrize("n,replica", [(3, True), (130, True), (258, True), (514, False)])
+def test_interleaved_l8_on_either_route(n, replica):
+    """Kept in LDS (130 chains with exchange), class passes (3, 258) or halves (514)."""
+    from paper_1509_08391_amd import llr
+    lats = [(8, n)]
+    got = []
+    for timing in (False, True):
+        ctx = _context(llr, lats, "f32", "interleaved", replica=replica)
+        ctx.hot_start()
+        ctx.approach()
+        ctx.set_timing(timing)
+        ctx.run()
+        out = [ctx.sweeps(3, sweep0=50, mode=llr.MODE_FREE)]
+        got.append(out + _results(ctx, lats))
+        ctx.close()
     _equal(*got)

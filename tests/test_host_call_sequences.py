@@ -121,3 +121,25 @@ k = calls()
 result = [sum(x[0] == "hipGraphLaunch" for x in k), sum(x[0] == "hipStreamWaitEvent" for x in k)]
 ''')
     assert got == [4, 0], got
+
+
+def test_interleaved_sweeps_of_l8_leave_lds_where_class_passes_are_faster(tmp_path):
+    got = run(tmp_path, '''
+result = {}
+def resident(h):
+    rec.rec_reset()
+    assert L.llr_rm_begin(h) == 0 and L.llr_rm_step(h, 1) == 0
+    names = [k[1] for k in calls() if k[0] == "launch"]
+    chain = any("k_chain" in n for n in names)
+    assert chain != any("k_hb" in n for n in names)
+    return chain
+for ex, counts in ((1, (1, 127, 128, 256, 257)), (0, (1, 512, 513))):
+    for n in counts:
+        result["%d %d" % (ex, n)] = resident(context(llr.FP32, [(8, n)], llr.SWEEP_INTERLEAVED, replica_exchange=ex))
+# other orders, smaller lattices and the rest of the calls are kept in LDS
+h = context(llr.FP32, [(8, 3)], llr.SWEEP_GROUPED, replica_exchange=1)
+result["grouped"] = resident(h)
+result["L=6"] = resident(context(llr.FP32, [(6, 3)], llr.SWEEP_INTERLEAVED, replica_exchange=1))
+''')
+    assert got == {"1 1": False, "1 127": False, "1 128": True, "1 256": True, "1 257": False,
+                   "0 1": True, "0 512": True, "0 513": False, "grouped": True, "L=6": True}, got
