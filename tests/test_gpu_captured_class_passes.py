@@ -74,3 +74,38 @@ def test_switch_between_iterations(switch, prec):
         ctx.close()
     for x, y in zip(*got):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("order", ["grouped", "interleaved", "staggered"])
+def test_short_iterations_of_a_large_run(order):
+    """Two sweeps an iteration: too short for halves, so captured whole; the staggered
+    order's graph holds both streams' launches and their fork and join."""
+    from paper_1509_08391_amd import llr
+    L, n = 14, 40
+    v6 = 6 * L ** 4
+    dE = 0.1 / n * v6
+    got = []
+    for graphs in (True, False):
+        ctx = llr.Context(precision=llr.FP32)
+        ctx.set_params(n_th=1, n_a=1, n_rm=5, seed=29, replica_exchange=True, recompute_every=3, approach_cap=4000)
+        ctx.set_sweep_order({"grouped": llr.SWEEP_GROUPED, "interleaved": llr.SWEEP_INTERLEAVED,
+                             "staggered": llr.SWEEP_STAGGERED}[order])
+        ctx.add_lattice(L, 0.58 * v6 + dE * np.arange(n), dE)
+        ctx.bind_state()
+        ctx.set_a(0, 1.0)
+        ctx.set_graphs(graphs)
+        ctx.hot_start()
+        ctx.approach()
+        ctx.set_tiles(2, 2)
+        ctx.enable_bits_log(32)
+        ctx.rm_begin()
+        E = []
+        for _ in range(5):
+            ctx.rm_step(1)
+            E.append(ctx.get_energy(0)[0])
+            ctx.recompute_energy()
+        out = [np.array(E), ctx.sweeps(2, sweep0=40, mode=llr.MODE_FREE)]
+        got.append(out + _results(ctx))
+        ctx.close()
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
