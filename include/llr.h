@@ -194,8 +194,9 @@ llr_status llr_set_restriction(llr_ctx *ctx, int per_link);
  *     context's and a second one of default priority), so that the heatbath
  *     passes, bound by vector instructions, overlap the overrelaxation passes,
  *     bound by memory; in small ones on the context's stream, one set's
- *     overrelaxation joined with the other's of the next sweep.  2 x 4V link updates per
- *     sweep, as grouped.
+ *     overrelaxation joined with the other's of the next sweep.
+ *     llr_observables and, while timing is on, every call uses both streams at
+ *     any size, sweep after sweep.  2 x 4V link updates per sweep, as grouped.
  * Applies to the restricted, free and multicanonical sweeps of llr_run /
  * llr_rm_step / llr_sweeps / llr_observables / the multicanonical run (whose
  * accepted classes then get heatbath-only dynamics in the interleaved order,
@@ -303,13 +304,14 @@ llr_status llr_set_tiles(llr_ctx *ctx, int hb_lpt, int or_lpt);
  * Results do not depend on it. */
 llr_status llr_set_order(llr_ctx *ctx, int serpentine);
 /* on != 0 (default): the sweeps of llr_run / llr_rm_step are captured once per
- * variant into HIP graphs and replayed, and large runs go through their sweeps in
- * two halves of the chains on two streams (the context's and a second one of
- * default priority, joined before the call returns its results).  0, and while
- * per-kernel timing is on: class pass after class pass.  Small lattices (L <= 8
- * in FP32, L <= 6 in FP64), kept in LDS, run any
- * number of sweeps per launch either way, except while timing is on.  Results do
- * not depend on any of it. */
+ * variant into HIP graphs and replayed, and large runs of more than a few sweeps
+ * go through them in two halves of the chains on two streams (the context's and a
+ * second one of default priority, joined before the call returns its results;
+ * llr_observables stays whole).  0, and while per-kernel timing is on: class pass
+ * after class pass.  A context of small lattices only (L <= 8 in FP32, L <= 6 in
+ * FP64) keeps its chains in LDS either way, except while timing is on and for some
+ * interleaved runs of L = 8, and runs up to 64 sweeps per launch, or one with
+ * replica exchange.  Results do not depend on any of it. */
 llr_status llr_set_graphs(llr_ctx *ctx, int on);
 /* One class pass of every chain: heatbath (heatbath != 0, acceptance by mode,
  * counters with sweep index sweep_index) or overrelaxation of colour c. */

@@ -17,10 +17,12 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # The sweep kernels are compiled without floating-point contraction: every
 # tile instantiation (links per thread) then performs the same IEEE
 # operations, so results do not depend on the autotuner's choice.
-EXTRA = {"llr_sweep.hip": ["-ffp-contract=off"], 
+EXTRA = {"llr_sweep.hip": ["-ffp-contract=off"],
          # the chain-resident kernel loops over the passes of a sweep; left in the
          # loop, the polynomials' constants cost an instruction each, hoisted out
-         # of it they fill the registers and spill
+         # of it they fill the registers and spill far more than the shapes that
+         # spill without it (16 to 47 registers with 4 links per thread, 10 to 30
+         # in the link mode)
          "llr_chain.hip": ["-ffp-contract=off", "-mllvm", "-disable-machine-licm"]}
 
 

@@ -95,7 +95,7 @@ struct llr_ctx {
     LatTable lt{};
     DevState ds{};
     bool laid_out = false;
-    bool resident = false;     // every lattice's chain fits in LDS (chain-resident sweeps)
+    bool resident = false;     // every lattice's chain fits in LDS (chain-resident sweeps: one launch holds all chains)
     bool resident_wide = false;   // a chain of L = 8 among them
     bool resident_link = false;   // with a class's candidates of the per-link restriction too
     void* state = nullptr;
@@ -111,7 +111,7 @@ struct llr_ctx {
     bool use_graphs = true;
     hipGraphExec_t sweep_graph[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     hipStream_t cap_stream = nullptr;  // default priority
-    hipStream_t side = nullptr;        // staggered order: the second chain set's stream (default priority)
+    hipStream_t side = nullptr;        // the second half's stream of staggered and pipelined sweeps (default priority)
     hipEvent_t fork_ev = nullptr, join_ev = nullptr, half_ev = nullptr;
     bool rm_open = false;
     // timing
@@ -634,9 +634,11 @@ static llr_status ensure_side_stream(llr_ctx* c);
 // the half sweep between the halves already and needs no more than this of a join.
 // In the interleaved order the fused passes of one half fill the ramps and last waves
 // of the other's; the halves join at the end of each sweep.  Half launches leave less
-// work to hide their own ramps and are twice as many: below kPipeLinks class links
+// work to hide their own ramps and are twice as many: below about kPipeLinks class links
 // (FP64 ones count four times, as their heatbath takes four times as long) whole
-// launches from captured graphs are as fast or faster.  Measured, us per sweep whole /
+// launches from captured graphs are as fast or faster.  One line for all orders and both
+// precisions is a compromise: just below it a grouped FP64 run (14 x 8) gives away 1 %
+// and an interleaved FP32 one (12 x 64) 5 %.  Measured, us per sweep whole /
 // halves, FP32: L = 20 x 128 1251 / 1076, 20 x 64 614 / 538, 18 x 24 243 / 205, 18 x
 // 16 (840 000 links) 191 / 174, 12 x 80 (830 000) 204 / 174, 10 x 160 (800 000) 191 /
 // 169, 14 x 40 (768 000) 191 / 171, 12 x 64 (664 000) 174 / 178, 10 x 128 (640 000)
@@ -789,7 +791,8 @@ static llr_status enqueue_pipelined(llr_ctx* c, int mode, const SweepRun& r) {
 // FP32 99 / 86 us, direct / replayed).  Us per sweep two streams / one, FP32:
 // L = 12 x 16 159..178 / 118, 10 x 32 156..171 / 119, 14 x 20 152..173 / 145, 20 x 8
 // 170 / 162, 12 x 64 171 / 172, 14 x 39 183 / 188; FP64: 8 x 64 204 / 172, 10 x 32
-// 216 / 194, 20 x 2 223 / 197.
+// 216 / 194, 20 x 2 223 / 197.  (The last FP32 ones, just below kPipeLinks, would be up
+// to 3 % faster on two streams; the rule has no line of its own for them.)
 static bool merged_stagger(const llr_ctx* c, int mode) {
     return c->stagger && plain_mode(mode) && !c->timing && c->use_graphs && !resident_sweeps(c, mode) &&
            two_halves(c) && !large_sweeps(c, mode);
@@ -827,10 +830,12 @@ static llr_status enqueue_merged_stagger(llr_ctx* c, int mode, const SweepRun& r
 static int restricted_mode(const llr_ctx* c) { return c->per_link ? LLR_MODE_LINK : LLR_MODE_RESTRICTED; }
 
 // One restricted sweep of the Robbins-Monro loop.  Without per-kernel timing
-// the 18-20 launches of a sweep (10-12 in the interleaved order) are captured
-// once per variant into a HIP graph
-// (kernel nodes only) and replayed; the sweep index lives in device memory, so
-// every replay advances it.
+// the launches of a sweep (16 class passes, 8 in the interleaved order, with the
+// sweep's end and a recompute 17-18 and 9-10; 2 where the chains are kept in LDS) are
+// captured once per variant into a HIP graph (kernel nodes only) and replayed; the
+// sweep index lives in device memory, so every replay advances it.  Staggered sweeps
+// come here where no lattice has a second half, and in large runs too short for the
+// pipelined halves, whose graphs hold both streams' launches with their fork and join.
 template <typename T>
 static llr_status launch_sweep(llr_ctx* c, bool recompute, bool replica, bool measure) {
     if (c->per_link) {   // before any capture: the first use allocates

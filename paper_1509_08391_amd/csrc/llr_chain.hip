@@ -567,7 +567,11 @@ __global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T
 // waits at a barrier; otherwise a chain gets up to 1024 threads, the shortest
 // chain of dependent work per pass.  Measured, us per sweep of L = 8 FP32 with
 // 1024 / 512 threads: 32 chains 70.3 / 78.7, 256 chains 71.2 / 80.0, 300
-// chains 140.5 / 121.3, 512 chains 141.1 / 123.2.
+// chains 140.5 / 121.3, 512 chains 141.1 / 123.2.  The 512-thread shape's four links
+// outgrow its 128 registers (16 spilled to 60 bytes of scratch per lane, 47 to 224 with
+// the fused overrelaxation), and so do the link mode's shapes (10 to 30, 28 to 112
+// bytes); the others have 0 to 36 bytes.  All chains of a context run in one launch,
+// so one lattice that does not fit leaves every lattice to the class passes.
 constexpr size_t kChainLds = 131072;
 constexpr uint32_t kChainLinksF64 = 1024;
 // Four lanes per link while the 4 x 128 links of L = 4 leave a CU's SIMDs two

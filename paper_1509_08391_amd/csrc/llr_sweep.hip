@@ -258,8 +258,10 @@ __device__ __forceinline__ void staple_sums(const LinkLoads<T>& q, T& C, T& S) {
 // scheduler saves registers by spreading them among the sums, one or two in
 // flight at a time (heatbath of L = 20 x 128, FP32: 133 us so, 92 with a link's
 // loads together, 88 with the next link's ahead).  Overrelaxation of L = 12 x 64
-// FP32: 8.7 -> 7.4 us; of L = 20 x 128 67 -> 64, 5.7 TB/s.  Links past the lattice's end (x3 >= L, uniform) load the
-// last one's and are not used.
+// FP32: 8.7 -> 7.4 us; of L = 20 x 128 67 -> 64, 5.7 TB/s.  Links past the lattice's
+// end (x3 >= L, uniform) load the last one's and are computed, not used: with 4 links
+// per thread a sixth of the links at L = 10, an eighth at L = 14, a tenth at L = 18,
+// which the tuner weighs against fewer links per thread.
 template <typename T, int MU, int LPT, int AHEAD>
 __device__ __forceinline__ void col_staples(const LatDev& L, const ChainBuf<T>& cb, uint64_t curw, int p,
                                             const ColTile& ct, const ColNbr& nb, T* C, T* S, T* t_old) {
@@ -321,8 +323,8 @@ __device__ __forceinline__ bool chain_arrive(unsigned long long* acc, long long 
 // theta' is formed as arg[(cos(pi V1/2) + i q sin(pi V1/2))^2 (C - i S)], and
 // the new local action is R cos X.
 //
-// Each thread owns the LPT class links of its column in a tile (all their
-// loads are issued before the arithmetic).  Sampler schedule: every link
+// Each thread owns the LPT class links of its column in a tile (a link's loads
+// are issued one link ahead of its staple sums).  Sampler schedule: every link
 // tries attempts 0 and 1 (one Philox call); the few links that reject both
 // are queued in LDS and later rounds give each queued link its next two
 // attempts with full lanes, so the lockstep cost of the acceptance tail is
@@ -545,7 +547,9 @@ __device__ __forceinline__ void hb_block(const LatTable& lt, T* __restrict__ th,
 }
 
 // With 4 class links per thread the registers are kept to 72 (FP32, seven
-// wavefronts per SIMD) and 128 (FP64, four), which they fit without spills.
+// wavefronts per SIMD) and 128 (FP64, four).  They fit without scratch memory but
+// for the fused FP64 pass, which spills two registers (12 bytes per lane); scalar
+// registers beyond the limit (24 to 102) are kept in lanes of vector ones.
 // The FP32 pass is bound by vector-instruction issue: 305 per class link (340
 // before the straight-line links and the buffer addressing), of which about 45
 // are a wavefront's prologue, queue and reduction shared by its 4 links.
