@@ -77,11 +77,6 @@ __device__ __forceinline__ ColTile col_tile(const LatDev& L, int tile, int tid) 
     t.x2 = (int)r2;
     return t;
 }
-__device__ __forceinline__ uint32_t half_of(const LatDev& L, int y0, int y1, int y2, int y3) {
-    return (uint32_t)((y0 >> 1) + L.hL * (y1 + L.L * (y2 + L.L * y3)));
-}
-__device__ __forceinline__ int up(int v, int L) { return v + 1 == L ? 0 : v + 1; }
-__device__ __forceinline__ int dn(int v, int L) { return v == 0 ? L - 1 : v - 1; }
 
 template <typename T>
 __device__ __forceinline__ T* chain_base(const LatDev& L, T* th, int cl) {
