@@ -511,7 +511,8 @@ __global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T
                 if (t >= a.measure_from) sumE += E;
                 if (a.E_hist) a.E_hist[(size_t)t * lt.n_chains + g] = E;
                 if (a.end_sweep) {
-                    const uint16_t b16 = (uint16_t)(bits | (a.approach ? 0u : 0xff00u));
+                    // the launch's first sweep takes what single class passes before it left
+                    const uint16_t b16 = (uint16_t)(bits | (t == 0 ? s.bits[g] : 0u) | (a.approach ? 0u : 0xff00u));
                     const long long row = row0 + t;
                     if (s.bits_log && row < s.bits_rows_max) s.bits_log[row * lt.n_chains + g] = b16;
                     s.bits_last[g] = b16;
@@ -533,6 +534,7 @@ __global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T
             s.hb_prop[g] += prop;
             s.hb_acc[g] += nacc;
             s.fu_acc[g] += nfused;
+            if (a.end_sweep) s.bits[g] = 0;
             if constexpr (VAR == kHbPre) {
                 s.link_fix[g] += fixes;
                 s.link_arc[g] += arcs;
@@ -540,9 +542,11 @@ __global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T
         }
     }
     if (idle && a.end_sweep && tid == 0) {
+        const uint16_t first = s.bits[g];
         for (int t = 0; t < a.n_sweeps; ++t)
-            if (s.bits_log && row0 + t < s.bits_rows_max) s.bits_log[(row0 + t) * lt.n_chains + g] = 0;
-        s.bits_last[g] = 0;
+            if (s.bits_log && row0 + t < s.bits_rows_max) s.bits_log[(row0 + t) * lt.n_chains + g] = t == 0 ? first : 0;
+        s.bits_last[g] = a.n_sweeps == 1 ? first : 0;
+        s.bits[g] = 0;
     }
     if (a.end_sweep && tid == 0) {
         // the block that arrives last advances the counters every block has read
@@ -570,7 +574,7 @@ __global__ __launch_bounds__(MAXT, GRP == 4 ? 2 : 4) void k_chain(LatTable lt, T
 // chains 140.5 / 121.3, 512 chains 141.1 / 123.2.  The 512-thread shape's four links
 // outgrow its 128 registers (16 spilled to 60 bytes of scratch per lane, 47 to 224 with
 // the fused overrelaxation), and so do the link mode's shapes (10 to 30, 28 to 112
-// bytes); the others have 0 to 36 bytes.  All chains of a context run in one launch,
+// bytes); the others have 0 to 20 bytes.  All chains of a context run in one launch,
 // so one lattice that does not fit leaves every lattice to the class passes.
 constexpr size_t kChainLds = 131072;
 constexpr uint32_t kChainLinksF64 = 1024;

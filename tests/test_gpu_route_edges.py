@@ -155,3 +155,33 @@ def test_interleaved_l8_on_either_route(n, replica):
         got.append(out + _results(ctx, lats))
         ctx.close()
     _equal(*got)
+
+
+@pytest.mark.parametrize("lats,prec", [([(4, 3)], "f64"), ([(6, 2), (4, 3)], "f32")])
+def test_class_pass_bits_reach_the_next_sweep(lats, prec):
+    """A single class pass leaves its accept bit for the next sweep's record, whichever
+    route that sweep takes, and for that one only."""
+    from paper_1509_08391_amd import llr
+    got = []
+    for timing in (False, True):
+        ctx = _context(llr, lats, prec, "grouped", n_th=1, n_a=2)
+        ctx.hot_start()
+        ctx.approach()
+        ctx.set_timing(timing)
+        ctx.enable_bits_log(64)
+        out = []
+        for colour in (2, 5):
+            ctx.class_pass(1, colour, mode=llr.MODE_FREE, sweep_index=900 + colour)
+            out.append(ctx.sweeps(3, sweep0=10 * colour))
+            ctx.class_pass(1, colour, mode=llr.MODE_FREE, sweep_index=920 + colour)
+            ctx.approach_begin()
+            out.append(ctx.approach_continue(10)[0])
+            out.append(ctx.sweeps(1, sweep0=100, mode=llr.MODE_APPROACH))
+        ctx.class_pass(1, 7, mode=llr.MODE_FREE, sweep_index=940)
+        ctx.rm_begin()
+        ctx.rm_step(1)
+        out += [ctx.get_bits_log(), ctx.export_state(0).cpu().numpy(), *ctx.get_energy(0)]
+        got.append(out)
+        ctx.close()
+    assert np.all(got[0][0][0] & 4)
+    _equal(*got)
