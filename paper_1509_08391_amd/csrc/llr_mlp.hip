@@ -245,9 +245,10 @@ __global__ __launch_bounds__(kMB) void k_mlp_epoch(MlpBuf in, MlpBuf out, const 
     for (int e = t; e < kRows * H; e += kMB) {
         const int i = e / H, k = e - i * H;
         d2[i][k] = i < nr ? dy[i] * net.w3[k] * (1.f - c.h2[i][k] * c.h2[i][k]) : 0.f;
-        // (tanh(0 w + b2) in the rows past the last sample: not a number for an infinite w)
-        if (i >= nr) c.h2[i][k] = 0.f;
     }
+    // (tanh(0 w + b2) in the rows past the last sample: not a number for an infinite w)
+    if (nr < kRows)
+        for (int e = nr * H + t; e < kRows * H; e += kMB) c.h2[e / H][e % H] = 0.f;
     __syncthreads();
     // output layer, biases and the loss, on a wavefront each; the rows past the
     // last sample hold zeros (dy, h2, d2, d1, lpart), so every sum runs over all rows
